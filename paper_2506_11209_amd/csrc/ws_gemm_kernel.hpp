@@ -30,17 +30,14 @@
 //    second half loads B, concurrently (two DMA warps, one tile each).
 //  * Consumers read operands with ds_read_b128 (A, K-contiguous) and
 //    ds_read_b64_tr_b16 (B, N-contiguous, transposed by the read) and
-//    accumulate with v_mfma_f32_32x32x16_{bf16,f16} in fp32.  In the plain
-//    kernels the K loop of a tile is a generated asm block (ws_deep_loop.inc,
-//    configurations listed in gen_deep_loop.py): with two consumer waves per
-//    SIMD (eight consumer waves, or four at 128 x 128 x 32 with two
-//    workgroups per CU) the register-lean roll loop (consumer_roll, also in
-//    the event-traced twin), with one the deep-prefetch loop that keeps the
-//    reads of the next three k-steps in flight behind the MFMAs
-//    (consumer_deep: 1:1 tiles of 64x128 and up at TK = 64 and 128x256x32,
-//    2:1 tiles up to 128x128).  The other shapes, the general variant, the
-//    traced twins of the deep-prefetch kernels and the 2:1 kernels of the
-//    largest four-consumer tiles run compiler-scheduled consumers.
+//    accumulate with v_mfma_f32_32x32x16_{bf16,f16} in fp32.  The K loop of a
+//    tile is a generated asm block, in the plain and in the general kernels:
+//    with one or four consumer waves the streaming loop (consumer_stream,
+//    ws_stream_loop.inc, configurations in gen_stream_loop.py), with eight
+//    (two per SIMD) the register-lean roll loop (consumer_roll,
+//    ws_deep_loop.inc, gen_deep_loop.py; also in its event-traced twin and in
+//    that of the four-consumer 128 x 128 x 32 kernel).  The other traced twins
+//    run compiler-scheduled consumers.
 //  * The grid is persistent: at most one workgroup per CU slot, each walking
 //    output tiles in dispatch rounds (Section 2.1, "Wave").  The tile order
 //    places the tiles that run at the same time on one XCD next to each
@@ -193,6 +190,43 @@ constexpr bool swz_a_step_invariant(int step) {
   return true;
 }
 
+// B tile layout: k-row and first column, inside the tile, of the 16-byte chunk
+// stored at byte 16 q.
+template <int TN>
+__host__ __device__ constexpr int b_chunk_row(int q) {
+  return (q >> 3) / (TN / 16) * 4 + ((q & 7) >> 1);
+}
+template <int TN>
+__host__ __device__ constexpr int b_chunk_col(int q) {
+  return (q >> 3) % (TN / 16) * 16 + (q & 1) * 8;
+}
+
+// Byte offset, inside the B tile, of a lane's transposed 8-byte read of
+// k-step 0 in the 32 columns from `col` (a multiple of 32): 16-lane group g
+// takes k-rows 8 (g / 2) .. 8 (g / 2) + 3 and the column half g % 2, lane j of
+// the group 8 bytes (columns 4 (j % 4) ..) of row j / 4.
+template <int TN>
+__host__ __device__ constexpr uint32_t b_read_off(int lane, int col) {
+  const int g = lane >> 4, j = lane & 15;
+  return (uint32_t)(((2 * (g >> 1)) * (TN / 32) + col / 32) * 256 + (g & 1) * 128 + j * 8);
+}
+
+// Every read lands on the chunk that holds its row and columns.
+template <int TN>
+constexpr bool b_layout_consistent() {
+  for (int lane = 0; lane < 64; ++lane)
+    for (int col = 0; col < TN; col += 32) {
+      const int off = (int)b_read_off<TN>(lane, col), q = off >> 4;
+      const int row = 8 * (lane >> 5) + ((lane & 15) >> 2);
+      const int c = col + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      if (b_chunk_row<TN>(q) != row || b_chunk_col<TN>(q) + (off & 15) / 2 != c) return false;
+    }
+  return true;
+}
+static_assert(b_layout_consistent<32>() && b_layout_consistent<64>() && b_layout_consistent<128>() &&
+                  b_layout_consistent<256>(),
+              "B chunks and B reads must agree");
+
 __device__ __forceinline__ uint32_t lds_peek(WSG_LDS uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -217,12 +251,12 @@ __device__ __forceinline__ void wait_vmcnt() {
 // out of order, but one in flight only makes the wait stricter: the count
 // bounds LDS and scalar operations together, so when it is at most YOUNGER
 // at most YOUNGER LDS operations are outstanding, and those are the youngest.
-template <int YOUNGER = 0>
+template <int YOUNGER = 0, int COUNT = 1>
 __device__ __forceinline__ void lds_signal(WSG_LDS uint32_t* p) {
   static_assert(YOUNGER >= 0 && YOUNGER <= 15, "lgkmcnt range");
 #if defined(__HIP_DEVICE_COMPILE__)
   const uint32_t addr = (uint32_t)(uintptr_t)p;
-  const uint32_t one = 1u;
+  const uint32_t one = COUNT;
   uint64_t saved;
   asm volatile(
       "s_waitcnt lgkmcnt(%3)\n\t"
@@ -241,11 +275,12 @@ __device__ __forceinline__ void lds_signal(WSG_LDS uint32_t* p) {
 // the wave's own LDS writes), so it costs no LDS round trip of its own.
 // Returns the value read (wave-uniform); the counters are monotonic, so a
 // value that already satisfies a later wait stays valid.
+template <int COUNT = 1>
 __device__ __forceinline__ uint32_t lds_signal_peek(WSG_LDS uint32_t* p, WSG_LDS uint32_t* peek) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const uint32_t addr = (uint32_t)(uintptr_t)p;
   const uint32_t paddr = (uint32_t)(uintptr_t)peek;
-  const uint32_t one = 1u;
+  const uint32_t one = COUNT;
   uint64_t saved;
   uint32_t v;
   asm volatile(
@@ -260,7 +295,7 @@ __device__ __forceinline__ uint32_t lds_signal_peek(WSG_LDS uint32_t* p, WSG_LDS
       : "memory");
   return __builtin_amdgcn_readfirstlane(v);
 #else
-  *p += 1;
+  *p += COUNT;
   return *peek;
 #endif
 }
@@ -738,6 +773,16 @@ __device__ __forceinline__ bool traced_workgroup(const KernelArgs& args) {
   return args.trace != nullptr && (int)blockIdx.x < args.trace_wgs;
 }
 
+// A wave's place in the ring as LDS byte addresses: the slot it reads, the
+// full counter (and target) of the K-iteration it looks at next and the empty
+// counter it signals next, each wrapping at the end of its range.
+struct RingCursor {
+  uint32_t slot, full, target, empty;
+  uint32_t ring, ring_end, full0, full_end, empty0, empty_end, abort_flag;
+};
+
+#include "ws_stream_loop.inc"
+
 // ---------------------------------------------------------------------------
 // Producer (DMA warp).  Waits for a free slot, streams its share of the A
 // and/or B tile of one K-iteration into that slot, and signals the slot full
@@ -762,12 +807,14 @@ __device__ __forceinline__ void wait_landed(uint32_t n) {
   }
 }
 
-template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, bool TRACE, bool DO_A, bool DO_B>
+template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, bool TRACE, bool DO_A, bool DO_B,
+          int GROUPS>
 __device__ __forceinline__ void producer_loop(const KernelArgs& args, WSG_LDS char* smem,
                                               int a_rank, int b_rank, int lane) {
   using G = Cfg<TM, TN, TK, NC, NPW, SPLIT, BF16>;
-  constexpr int A_GROUP = (SPLIT == 1) ? G::NP : G::NP / 2;  // waves sharing the A tile
-  constexpr int B_GROUP = (SPLIT == 1) ? G::NP : G::NP / 2;
+  // waves sharing the A (B) tile of one K-iteration
+  constexpr int A_GROUP = ((SPLIT == 1) ? G::NP : G::NP / 2) / GROUPS;
+  constexpr int B_GROUP = A_GROUP;
   constexpr int A_PER = DO_A ? G::A_INSTR / A_GROUP : 0;     // DMA instructions per wave
   constexpr int B_PER = DO_B ? G::B_INSTR / B_GROUP : 0;
   constexpr int LOADS = A_PER + B_PER;
@@ -779,6 +826,9 @@ __device__ __forceinline__ void producer_loop(const KernelArgs& args, WSG_LDS ch
   WSG_LDS uint32_t* empty = full + kMaxStages;
   WSG_LDS uint32_t* abort_flag = full + 2 * kMaxStages;
   const int K = args.K, N = args.N;
+  const uint32_t grp = (uint32_t)(DO_A ? a_rank : b_rank) / (uint32_t)A_GROUP;  // this wave's group
+  a_rank %= A_GROUP;
+  b_rank %= B_GROUP;
 
   // Byte offset, inside the tile, of the 16-byte chunk this lane fetches for
   // each of its DMA instructions (the LDS side is fixed: lane l writes bytes
@@ -794,41 +844,52 @@ __device__ __forceinline__ void producer_loop(const KernelArgs& args, WSG_LDS ch
 #pragma unroll
   for (int n = 0; n < B_PER; ++n) {
     const int q = (b_rank + n * B_GROUP) * 64 + lane;
-    const int blk = q >> 3, w = q & 7;
-    const int kq = blk / G::NQ, nq = blk % G::NQ;
-    b_goff[n] = (uint32_t)((kq * 4 + (w >> 1)) * N + nq * 16 + (w & 1) * 8) * 2u;
+    b_goff[n] = (uint32_t)(b_chunk_row<TN>(q) * N + b_chunk_col<TN>(q)) * 2u;
   }
 
   // TRACE: this instance runs only in workgroups that record events.
   constexpr bool tracing = TRACE;
+  static_assert(!TRACE || GROUPS == 1, "the traced producers take every K-iteration");
   ProducerStamps<TRACE && NC == 8> stamps(args, DO_A && a_rank == 0, DO_B && b_rank == 0, lane);
-  // signal(): data of the slot has landed; stamp its landing time first when tracing.
-  auto publish = [&](uint32_t pq) {
-    const uint32_t pslot = ring_slot(pq, (uint32_t)args.stages);
-    if constexpr (tracing) stamps.landed(pq, cycles32(), &full[kStampLandA + pslot], &full[kStampLandB + pslot]);
-    lds_signal(&full[pslot]);
-  };
   const int Gd = gridDim.x;
   const uint32_t P = (uint32_t)args.stages;
-  uint32_t lag = P > 3 ? P - 2 : 1;
+  // signal() of K-iteration q_sig, whose data has landed (landing time stamped
+  // first when tracing).
+  uint32_t q_sig = grp, s_slot = grp;  // next K-iteration to signal and its slot
+  auto publish = [&]() {
+    if constexpr (tracing) stamps.landed(q_sig, cycles32(), &full[kStampLandA + s_slot], &full[kStampLandB + s_slot]);
+    lds_signal<0, GROUPS>(&full[s_slot]);
+    q_sig += GROUPS;
+    s_slot += GROUPS;
+    if (s_slot >= P) s_slot -= P;
+  };
+  const uint32_t S = (uint32_t)args.iters;
+  // K-iterations of this wave issued ahead of the one it signals
+  uint32_t lag = GROUPS > 1 ? P / GROUPS - 1 : (P > 3 ? P - 2 : 1);
   if (lag > (uint32_t)MAX_LAG) lag = MAX_LAG;
-  uint32_t q = 0;      // next K-iteration to issue
-  uint32_t q_sig = 0;  // next K-iteration to signal
-  for (int v = first_slot(args); v < args.num_tiles; v += Gd) {
+  const int g0 = first_slot(args);
+  const int my_tiles = g0 < args.num_tiles ? (args.num_tiles - g0 + Gd - 1) / Gd : 0;
+  const uint32_t total = (uint32_t)my_tiles * S;
+  // next K-iteration to issue, its slot and the empty[] value that use needs
+  // (0 for a slot's first use)
+  uint32_t q = grp, slot = grp, need = 0;
+  uint32_t kk = grp;
+  for (int v = g0; q < total; v += Gd) {
+    if (GROUPS > 1 && kk >= S) {  // a tile without K-iterations of this group
+      kk -= S;
+      continue;
+    }
     int ti, tj;
     tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
     const uint16_t* a_tile = args.A + (int64_t)ti * TM * K;
     const uint16_t* b_tile = args.B + (int64_t)tj * TN;
-    for (int kk = 0; kk < args.iters; ++kk, ++q) {
-      const uint32_t slot = ring_slot(q, P);
-      if (ring_use(q, P) > 0) {
+    for (; kk < S; kk += GROUPS, q += GROUPS) {
+      if (need > 0) {
         // wait(): the slot is free once every consumer wave released its previous use.
-        const uint32_t need = ring_empty_target(q, P, NC);
         if ((int32_t)(lds_read_now(&empty[slot]) - need) < 0) {
           while (q_sig < q) {  // publish pending iterations first, oldest first
-            wait_landed<LOADS>(q - q_sig - 1);
-            publish(q_sig);
-            ++q_sig;
+            wait_landed<LOADS>((q - q_sig) / GROUPS - 1);
+            publish();
           }
           if (!wait_counter(&empty[slot], need, abort_flag, args.spin_limit, args.err)) {
             wait_vmcnt<0>();  // no DMA into LDS may outlive the wave
@@ -854,17 +915,21 @@ __device__ __forceinline__ void producer_loop(const KernelArgs& args, WSG_LDS ch
           panel_load16_lds(src, (WSG_LDS void*)(b_dst + (b_rank + n * B_GROUP) * 1024), b_goff[n]);
       }
       // signal(): iteration q - lag has landed once at most `lag` newer ones are in flight.
-      if (q + 1 - q_sig > lag) {
+      if ((q - q_sig) / GROUPS + 1 > lag) {
         wait_landed<LOADS>(lag);
-        publish(q_sig);
-        ++q_sig;
+        publish();
+      }
+      slot += GROUPS;
+      if (slot >= P) {  // P >= 2 = the most groups: one lap at most
+        slot -= P;
+        need += NC;
       }
     }
+    kk -= S;
   }
   while (q_sig < q) {
-    wait_landed<LOADS>(q - q_sig - 1);
-    publish(q_sig);
-    ++q_sig;
+    wait_landed<LOADS>((q - q_sig) / GROUPS - 1);
+    publish();
   }
   stamps.finish();
 }
@@ -879,28 +944,39 @@ __device__ __forceinline__ void producer_loop(const KernelArgs& args, WSG_LDS ch
 // it idle.  The LDS layout is the one the LDS-DMA producer writes.
 // ---------------------------------------------------------------------------
 template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, bool TRACE, bool DO_A, bool DO_B,
-          bool GENERAL>
+          bool GENERAL, int GROUPS>
 __device__ __forceinline__ void producer_loop_reg(const KernelArgs& args, WSG_LDS char* smem,
                                                   int a_rank, int b_rank, int lane) {
   using G = Cfg<TM, TN, TK, NC, NPW, SPLIT, BF16>;
-  constexpr int A_GROUP = (SPLIT == 1) ? G::NP : G::NP / 2;
-  constexpr int B_GROUP = (SPLIT == 1) ? G::NP : G::NP / 2;
+  // Waves sharing the A (B) tile of one K-iteration: of the waves that load
+  // A (B), one of GROUPS groups, which take the K-iterations in turn.
+  constexpr int A_GROUP = ((SPLIT == 1) ? G::NP : G::NP / 2) / GROUPS;
+  constexpr int B_GROUP = A_GROUP;
   constexpr int A_PER = DO_A ? G::A_INSTR / A_GROUP : 0;
   constexpr int B_PER = DO_B ? G::B_INSTR / B_GROUP : 0;
   constexpr int LOADS = A_PER + B_PER;
   // VGPRs for staged tiles: what the consumers' allocation leaves (256 a wave
   // with eight waves, 168 with twelve; the 128 x 128 x 32 kernel held to 128
   // registers stages its cap of six K-iterations in 96)
-  constexpr int STAGE_VGPRS = (G::NW <= 8) ? 152 : (NC == 8 ? 128 : 96);
+  constexpr bool LEAN = StreamLoop<TM, TN, TK, NC, NPW, BF16>::kVgprs == 128;
+  constexpr int STAGE_VGPRS = LEAN ? (GENERAL ? 64 : 96) : (G::NW <= 8) ? 152 : (NC == 8 ? 128 : 96);
   constexpr int L0 = STAGE_VGPRS / (4 * LOADS);
   constexpr int L1 = (63 / LOADS) < L0 ? (63 / LOADS) : L0;
-  constexpr int L = L1 < 1 ? 1 : (L1 > 6 ? 6 : L1);  // K-iterations staged in VGPRs
+  constexpr int LCAP = 6 / GROUPS;
+  constexpr int L = L1 < 1 ? 1 : (L1 > LCAP ? LCAP : L1);  // of its K-iterations, staged in VGPRs
+  // With one K-iteration staged, each register is loaded again right behind
+  // the write that empties it, so that the loads in flight never run out; with
+  // more, the loads follow the signal, which they would only delay.
+  constexpr bool CHUNKWISE = L == 1;
   static_assert(G::A_INSTR % A_GROUP == 0 && G::B_INSTR % B_GROUP == 0, "even split");
 
   WSG_LDS uint32_t* full = (WSG_LDS uint32_t*)smem;
   WSG_LDS uint32_t* empty = full + kMaxStages;
   WSG_LDS uint32_t* abort_flag = full + 2 * kMaxStages;
   const int K = args.K, N = args.N;
+  const uint32_t grp = (uint32_t)(DO_A ? a_rank : b_rank) / (uint32_t)A_GROUP;  // this wave's group
+  a_rank %= A_GROUP;
+  b_rank %= B_GROUP;
 
   uint32_t goff[LOADS];  // byte offset of this lane's 16-byte chunk in the A / B tile
 #pragma unroll
@@ -912,9 +988,7 @@ __device__ __forceinline__ void producer_loop_reg(const KernelArgs& args, WSG_LD
 #pragma unroll
   for (int n = 0; n < B_PER; ++n) {
     const int q = (b_rank + n * B_GROUP) * 64 + lane;
-    const int blk = q >> 3, w = q & 7;
-    const int kq = blk / G::NQ, nq = blk % G::NQ;
-    goff[A_PER + n] = (uint32_t)((kq * 4 + (w >> 1)) * N + nq * 16 + (w & 1) * 8) * 2u;
+    goff[A_PER + n] = (uint32_t)(b_chunk_row<TN>(q) * N + b_chunk_col<TN>(q)) * 2u;
   }
   // The general variant needs registers for its edge tests: where a wave's
   // successive A (B) instructions lie a whole number of swizzle periods
@@ -932,12 +1006,13 @@ __device__ __forceinline__ void producer_loop_reg(const KernelArgs& args, WSG_LD
     const int qa = a_rank * 64 + lane;
     a_kc0 = 8 * ((qa % G::CA) ^ swz_a<TK>(qa / G::CA));
     const int qb = b_rank * 64 + lane;
-    b_nc0 = ((qb >> 3) % G::NQ) * 16 + (qb & 1) * 8;
+    b_nc0 = b_chunk_col<TN>(qb);
   }
   const uint32_t lane16 = (uint32_t)lane * 16u;
 
   // TRACE: this instance runs only in workgroups that record events.
   constexpr bool tracing = TRACE;
+  static_assert(!TRACE || GROUPS == 1, "the traced producers take every K-iteration");
   ProducerStamps<TRACE && NC == 8> stamps(args, DO_A && a_rank == 0, DO_B && b_rank == 0, lane);
   const int Gd = gridDim.x;
   const int g0 = first_slot(args);
@@ -946,108 +1021,117 @@ __device__ __forceinline__ void producer_loop_reg(const KernelArgs& args, WSG_LD
   const uint32_t total = (uint32_t)my_tiles * S;
   const uint32_t P = (uint32_t)args.stages;
 
-  // Issue cursor: the next K-iteration whose loads go out.
+  // Issue cursor: the next K-iteration whose loads go out (its A and B panel
+  // addresses move with it).
   int v_i = g0, ti_i = 0, tj_i = 0;
-  uint32_t kk_i = 0, q_iss = 0;
-  tile_coords(v_i, args.tiles_m, args.tiles_n, args.group_m, &ti_i, &tj_i);
+  uint32_t kk_i = 0, q_iss = grp;
+  const char* a_src = nullptr;
+  const char* b_src = nullptr;
+  const int64_t a_adv = (int64_t)TK * 2 * GROUPS, b_adv = (int64_t)TK * 2 * GROUPS * N;
+  auto point = [&]() {
+    tile_coords(v_i, args.tiles_m, args.tiles_n, args.group_m, &ti_i, &tj_i);
+    a_src = (const char*)(args.A + (int64_t)ti_i * TM * K + kk_i * TK);
+    b_src = (const char*)(args.B + (int64_t)kk_i * TK * N + (int64_t)tj_i * TN);
+  };
+  if (GROUPS > 1 && q_iss < total) {
+    kk_i = q_iss;
+    while (kk_i >= S) {
+      kk_i -= S;
+      v_i += Gd;
+    }
+  }
+  point();
 
   i32x4_t stage[L][LOADS];
   // Traced: one clock reading per K-iteration, taken once K-iteration q is in
   // its slot, stands for the landing of q and the issue of q + L (the loads
   // go out right after q's signal).
   uint32_t t_issue[L], t_now = 0;
-  // Loads go out unconditionally (past the last K-iteration they re-read the
-  // last valid tile and are never written to LDS), so every path through the
-  // loop has the same number of loads in flight and the compiler's vmcnt
-  // waits before each ds_write allow exactly L - 1 newer iterations.
-  auto issue = [&](int u) {
-    if constexpr (tracing) t_issue[u] = t_now;
-    const char* a_src = (const char*)(args.A + (int64_t)ti_i * TM * K + kk_i * TK);
-    const char* b_src = (const char*)(args.B + (int64_t)kk_i * TK * N + (int64_t)tj_i * TN);
-    // GENERAL: rows, columns and K left from this K-iteration's tile origin
-    // (wave-uniform; the origin is always inside A and B)
-    int rows_left = 0, cols_left = 0, k_left = 0;
+  __amdgpu_buffer_rsrc_t ra, rb;
+  uint32_t ab = 0, bb = 0;
+  int k_left = 0, cols_left = 0;
+  // Descriptors of the K-iteration under the issue cursor.
+  auto aim = [&]() {
     if constexpr (GENERAL) {
-      rows_left = args.M - ti_i * TM;
+      // rows, columns and K left from this K-iteration's tile origin
+      // (wave-uniform; the origin is always inside A and B); the record
+      // counts end at the last row of A (the last K row of B); offsets stay
+      // 16-byte multiples, so no chunk straddles the end
+      const int rows_left = args.M - ti_i * TM;
       cols_left = N - tj_i * TN;
       k_left = K - (int)kk_i * TK;
-    }
-    // GENERAL: the record counts end at the last row of A (the last K row
-    // of B); offsets stay 16-byte multiples, so no chunk straddles the end
-    const __amdgpu_buffer_rsrc_t ra =
-        GENERAL ? panel_rsrc_to_end(a_src, ((int64_t)rows_left * K - (int64_t)kk_i * TK) * 2)
-                : panel_rsrc(a_src);
-    const __amdgpu_buffer_rsrc_t rb =
-        GENERAL ? panel_rsrc_to_end(b_src, ((int64_t)k_left * N - (int64_t)tj_i * TN) * 2)
-                : panel_rsrc(b_src);
-    if (GENERAL) {
-      // K and N are multiples of 8, so a 16-byte chunk is wholly inside or
-      // wholly outside A / B.  Rows of A past M and K rows of B past K lie
-      // beyond the record counts, and a chunk past K in A (past N in B)
-      // loads from kOutsidePanel; the range check returns zeros for both, so
-      // partial tiles and the tail of the last K-iteration contribute
-      // nothing.  The test runs on every K-iteration, interior ones included: a branch
-      // between an interior and an edge form of these loads gives the
-      // compiler's wait-count analysis a path with fewer loads in flight,
-      // and it then waits for all of them before each slot write.
+      ra = panel_rsrc_to_end(a_src, ((int64_t)rows_left * K - (int64_t)kk_i * TK) * 2);
+      rb = panel_rsrc_to_end(b_src, ((int64_t)k_left * N - (int64_t)tj_i * TN) * 2);
       if constexpr (kStrided) {
-        // From the lane's first chunks and the steps.  A lane whose K chunk
-        // of A (column chunk of B) is past K (N) starts at kOutsidePanel,
-        // and every chunk offset from there stays below 2^32
-        // (a step times the chunk index is below 2^31).  The opaque copies
-        // keep the compiler from hoisting one offset per chunk out of the
-        // loop (they would not fit in the registers left).
-        uint32_t ab = goff[0], bb = goff[A_PER];
+        ab = goff[0];
+        bb = goff[A_PER];
         asm volatile("" : "+v"(ab), "+v"(bb));
         ab = a_kc0 < k_left ? ab : kOutsidePanel;
         bb = b_nc0 < cols_left ? bb : kOutsidePanel;
-#pragma unroll
-        for (int n = 0; n < A_PER; ++n) stage[u][n] = panel_load16(ra, ab + (uint32_t)n * a_step);
-#pragma unroll
-        for (int n = 0; n < B_PER; ++n) stage[u][A_PER + n] = panel_load16(rb, bb + (uint32_t)n * b_step);
-      } else {
-#pragma unroll
-        for (int n = 0; n < A_PER; ++n) {
-          const int q = (a_rank + n * A_GROUP) * 64 + lane;
-          const int kc = 8 * ((q % G::CA) ^ swz_a<TK>(q / G::CA));
-          stage[u][n] = panel_load16(ra, kc < k_left ? goff[n] : kOutsidePanel);
-        }
-#pragma unroll
-        for (int n = 0; n < B_PER; ++n) {
-          const int q = (b_rank + n * B_GROUP) * 64 + lane;
-          const int nc8 = ((q >> 3) % G::NQ) * 16 + (q & 1) * 8;
-          stage[u][A_PER + n] = panel_load16(rb, nc8 < cols_left ? goff[A_PER + n] : kOutsidePanel);
-        }
       }
     } else {
-#pragma unroll
-      for (int n = 0; n < A_PER; ++n) stage[u][n] = panel_load16(ra, goff[n]);
-#pragma unroll
-      for (int n = 0; n < B_PER; ++n) stage[u][A_PER + n] = panel_load16(rb, goff[A_PER + n]);
+      ra = panel_rsrc(a_src);
+      rb = panel_rsrc(b_src);
     }
-    if (q_iss + 1 < total) {
-      ++q_iss;
-      if (++kk_i == S) {
-        kk_i = 0;
-        v_i += Gd;
-        tile_coords(v_i, args.tiles_m, args.tiles_n, args.group_m, &ti_i, &tj_i);
+  };
+  auto load = [&](int u, int n) {
+    if constexpr (GENERAL) {
+      if constexpr (kStrided) {
+        stage[u][n] = n < A_PER ? panel_load16(ra, ab + (uint32_t)n * a_step)
+                                : panel_load16(rb, bb + (uint32_t)(n - A_PER) * b_step);
+      } else if (n < A_PER) {
+        const int q = (a_rank + n * A_GROUP) * 64 + lane;
+        const int kc = 8 * ((q % G::CA) ^ swz_a<TK>(q / G::CA));
+        stage[u][n] = panel_load16(ra, kc < k_left ? goff[n] : kOutsidePanel);
+      } else {
+        const int q = (b_rank + (n - A_PER) * B_GROUP) * 64 + lane;
+        const int nc8 = b_chunk_col<TN>(q);
+        stage[u][n] = panel_load16(rb, nc8 < cols_left ? goff[n] : kOutsidePanel);
+      }
+    } else {
+      stage[u][n] = panel_load16(n < A_PER ? ra : rb, goff[n]);
+    }
+  };
+  // Loads go out unconditionally (past the last K-iteration they re-read the
+  // last valid tile and are never written to LDS), so every path through the
+  // loop has the same number of loads in flight and the compiler's vmcnt
+  // waits before each ds_write allow exactly the newer ones.
+  auto advance = [&]() {
+    if (q_iss + GROUPS < total) {
+      q_iss += GROUPS;
+      kk_i += GROUPS;
+      a_src += a_adv;
+      b_src += b_adv;
+      if (kk_i >= S) {
+        do {
+          kk_i -= S;
+          v_i += Gd;
+        } while (GROUPS > 1 && kk_i >= S);
+        point();
       }
     }
   };
 
   if constexpr (tracing) t_now = cycles32();
 #pragma unroll
-  for (int u = 0; u < L; ++u) issue(u);
+  for (int u = 0; u < L; ++u) {
+    if constexpr (tracing) t_issue[u] = t_now;
+    aim();
+#pragma unroll
+    for (int n = 0; n < LOADS; ++n) load(u, n);
+    advance();
+  }
 
   // Slot of the next K-iteration to write, the empty[] value its use needs
   // (0 for a slot's first use), and the value of that counter read with the
   // previous signal: when the consumers are ahead it already satisfies the
   // wait, and the wave skips an LDS round trip.
-  uint32_t w_slot = 0, w_need = 0, seen = 0;
-  for (uint32_t q0 = 0; q0 < total; q0 += L) {
+  uint32_t w_slot = grp, w_need = 0, seen = 0;
+  for (uint32_t q0 = grp; q0 < total; q0 += L * GROUPS) {
 #pragma unroll
     for (int u = 0; u < L; ++u) {
-      const uint32_t q = q0 + u;
+      const uint32_t q = q0 + u * GROUPS;
+      aim();
       if (q < total) {
       const uint32_t slot = w_slot;
       // No early exit when the wait fails (workgroup aborted, or this wait
@@ -1063,24 +1147,37 @@ __device__ __forceinline__ void producer_loop_reg(const KernelArgs& args, WSG_LD
       compiler_fence();
       WSG_LDS char* base = smem + kHeaderBytes + slot * G::STAGE + lane16;
 #pragma unroll
-      for (int n = 0; n < A_PER; ++n)
-        *(WSG_LDS i32x4_t*)(base + (a_rank + n * A_GROUP) * 1024) = stage[u][n];
-#pragma unroll
-      for (int n = 0; n < B_PER; ++n)
-        *(WSG_LDS i32x4_t*)(base + G::A_BYTES + (b_rank + n * B_GROUP) * 1024) = stage[u][A_PER + n];
+      for (int n = 0; n < LOADS; ++n) {
+        if (n < A_PER) *(WSG_LDS i32x4_t*)(base + (a_rank + n * A_GROUP) * 1024) = stage[u][n];
+        else *(WSG_LDS i32x4_t*)(base + G::A_BYTES + (b_rank + (n - A_PER) * B_GROUP) * 1024) = stage[u][n];
+        if constexpr (CHUNKWISE) {
+          __builtin_amdgcn_sched_barrier(0);
+          load(u, n);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
       if constexpr (tracing) {
         t_now = cycles32();
         stamps.issued(q, t_issue[u], &full[kStampIssueA + slot], &full[kStampIssueB + slot]);
         stamps.landed(q, t_now, &full[kStampLandA + slot], &full[kStampLandB + slot]);
+        t_issue[u] = t_now;
       }
-      if (++w_slot == P) {
-        w_slot = 0;
+      w_slot += GROUPS;
+      if (w_slot >= P) {
+        w_slot -= P;
         w_need += NC;
       }
       // waits for the LDS writes, signals, and reads the next slot's empty[]
-      seen = lds_signal_peek(&full[slot], &empty[w_slot]);
+      seen = lds_signal_peek<GROUPS>(&full[slot], &empty[w_slot]);
+      } else if constexpr (CHUNKWISE) {
+#pragma unroll
+        for (int n = 0; n < LOADS; ++n) load(u, n);
       }
-      issue(u);  // refill this register stage with K-iteration q + L
+      if constexpr (!CHUNKWISE) {
+#pragma unroll
+        for (int n = 0; n < LOADS; ++n) load(u, n);  // refill this register stage
+      }
+      advance();
     }
   }
   stamps.finish();
@@ -1100,12 +1197,14 @@ __device__ __forceinline__ void producer_signal_only(const KernelArgs& args, WSG
   const int my_tiles = g0 < args.num_tiles ? (args.num_tiles - g0 + Gd - 1) / Gd : 0;
   const uint32_t total = (uint32_t)my_tiles * (uint32_t)args.iters;
   const uint32_t P = (uint32_t)args.stages;
+  uint32_t slot = 0, need = 0;  // empty[] value this use of the slot needs
   for (uint32_t q = 0; q < total; ++q) {
-    const uint32_t slot = ring_slot(q, P);
-    if (ring_use(q, P) > 0 &&
-        !wait_counter(&empty[slot], ring_empty_target(q, P, NC), abort_flag, args.spin_limit, args.err))
-      return;
+    if (need > 0 && !wait_counter(&empty[slot], need, abort_flag, args.spin_limit, args.err)) return;
     lds_signal(&full[slot]);
+    if (++slot == P) {
+      slot = 0;
+      need += NC;
+    }
   }
 }
 
@@ -1115,14 +1214,16 @@ template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, bool ST
           bool GENERAL>
 __device__ __forceinline__ void producer_run(const KernelArgs& args, WSG_LDS char* smem, int a_rank, int b_rank,
                                              int lane) {
+  constexpr int GR = 1;
+  constexpr int GD = 1;
   if constexpr (GENERAL) {  // partial tiles possible: always register-staged
-    producer_loop_reg<TM, TN, TK, NC, NPW, SPLIT, BF16, STAMP, DO_A, DO_B, true>(args, smem, a_rank, b_rank,
-                                                                            lane);
+    producer_loop_reg<TM, TN, TK, NC, NPW, SPLIT, BF16, STAMP, DO_A, DO_B, true, GR>(args, smem, a_rank, b_rank,
+                                                                                lane);
   } else if (args.load_path == 1) {  // wave-uniform: 0 = register-staged, 1 = LDS-DMA
-    producer_loop<TM, TN, TK, NC, NPW, SPLIT, BF16, STAMP, DO_A, DO_B>(args, smem, a_rank, b_rank, lane);
+    producer_loop<TM, TN, TK, NC, NPW, SPLIT, BF16, STAMP, DO_A, DO_B, GD>(args, smem, a_rank, b_rank, lane);
   } else {
-    producer_loop_reg<TM, TN, TK, NC, NPW, SPLIT, BF16, STAMP, DO_A, DO_B, false>(args, smem, a_rank, b_rank,
-                                                                             lane);
+    producer_loop_reg<TM, TN, TK, NC, NPW, SPLIT, BF16, STAMP, DO_A, DO_B, false, GR>(args, smem, a_rank, b_rank,
+                                                                                 lane);
   }
 }
 
@@ -1211,11 +1312,8 @@ __device__ __forceinline__ void consumer(const KernelArgs& args, WSG_LDS char* s
     for (int s = 0; s < G::KS; ++s)
       a_off[s] = (uint32_t)(r * TK * 2 + (((2 * s + (lane >> 5)) ^ swz_a<TK>(r)) << 4));
   }
-  // B: 16-lane group g reads block (kq = 4s + 2(g>>1) + h, nq = (wn*WN + 32 nb)/16 + (g&1)),
-  // lane j of the group at byte 8j of the block.
-  const int grp = lane >> 4;
-  const uint32_t b_off =
-      (uint32_t)(((2 * (grp >> 1)) * G::NQ + (wn * G::WN) / 16 + (grp & 1)) * 128 + 8 * (lane & 15));
+  // B: 16-lane group g reads its half of block (kq = 4s + 2(g>>1) + h, nd = (wn*WN)/32 + nb).
+  const uint32_t b_off = b_read_off<TN>(lane, wn * G::WN);
 
   const int Gd = gridDim.x;
   const int g0 = first_slot(args);
@@ -1338,59 +1436,43 @@ __device__ __forceinline__ void consumer(const KernelArgs& args, WSG_LDS char* s
   }
 }
 
-// ---------------------------------------------------------------------------
-// Deep-prefetch consumer: the operands of k-step t are read during k-step
-// t - 3, so three k-steps of LDS reads stay in flight behind the MFMAs.  The K
-// loop of a tile is one generated asm block (DeepLoop, ws_deep_loop.inc,
-// written by gen_deep_loop.py): its fragment registers are fixed and every
-// wait on an LDS read is placed by hand.  A wave's LDS operations complete in
-// order, so a wait names how many younger LDS operations may still be
-// outstanding; waits cap at 15, the counter's range (a wait for fewer only
-// waits longer).
-//
-// Per k-step t of a tile (KS k-steps per K-iteration, T = S KS in all):
-//   * wait for the reads of k-step t;
-//   * if k-step t + 3 exists and starts a new K-iteration, check that
-//     K-iteration's slot is full (its counter was peeked when the read stream
-//     entered the previous slot; poll, draining every read, only when it is
-//     short) and peek at the next slot's counter; issue the reads of k-step
-//     t + 3, one ahead of each MFMA of k-step t;
-//   * when t + 2 ends a K-iteration, release that K-iteration's slot (its last
-//     reads went out two k-steps earlier).
-// The loop body is four k-steps, so a tile needs S KS divisible by 4
-// (DeepLoop::kIterQuantum); TK = 32 tiles with an odd S take the
-// compiler-scheduled consumer.  The tile's last four k-steps read nothing
-// ahead and drain; the epilogue follows, and the next tile starts with a
-// prologue (the reads of its first three k-steps).
-// ---------------------------------------------------------------------------
 #include "ws_deep_loop.inc"
 
+// ---------------------------------------------------------------------------
+// Streaming consumer: the generated StreamLoop block (ws_stream_loop.inc,
+// gen_stream_loop.py) runs the K loop of a tile.  What bounds a consumer wave
+// that is alone on its SIMD is issue: everything between two MFMAs beyond
+// seven instructions leaves the matrix core idle.  Math-only kernels, clocks
+// per K-iteration against the MFMAs' own (one wave per SIMD unless said), for
+// the loops this one replaced and now: 128x128x64 859 -> 644 (512), 256x128x64
+// 1357 -> 1175 (1024), 128x256x32 2:1 (single-buffered) 1756 -> 789 (512),
+// 128x128x32 with two workgroups per CU 866 -> 722 (512), 64x64x64 with two
+// 1277 -> 747 (256).  The GEMM of 128x256x32 2:1 on the LDS-DMA path
+// (4096x8192x2048) went from 210 to 164 us, of 64x64x64 at 4096^3 from 317 to
+// 277 us.
+// ---------------------------------------------------------------------------
 template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, int MODE, bool GENERAL>
-__device__ __forceinline__ void consumer_deep(const KernelArgs& args, WSG_LDS char* smem, int cw,
-                                              int lane) {
+__device__ __forceinline__ void consumer_stream(const KernelArgs& args, WSG_LDS char* smem, int cw,
+                                                int lane) {
   using G = Cfg<TM, TN, TK, NC, NPW, SPLIT, BF16>;
-  using Loop = DeepLoop<TM, TN, TK, NC, NPW, BF16>;
-  static_assert(Loop::kAvailable && (G::KS == 4 || G::KS == 2), "deep consumer configuration");
+  using Loop = StreamLoop<TM, TN, TK, NC, NPW, BF16>;
   constexpr int BM = G::BM, BN = G::BN;
+  // old C rows the general epilogue loads together: as registers allow
+  constexpr int EG = G::NW > 8 ? 1 : Loop::kVgprs == 128 ? 4 : (BN > 2 ? 32 / BN : 16);
   WSG_LDS uint32_t* full = (WSG_LDS uint32_t*)smem;
   WSG_LDS uint32_t* empty = full + kMaxStages;
   WSG_LDS uint32_t* abort_flag = full + 2 * kMaxStages;
 
   const int wm = cw / G::WGN, wn = cw % G::WGN;
-  // A operand of k-step s: row r, 16-byte chunk (2 s + lane / 32) ^ swz(r).
-  // Slots start on 128-byte boundaries, so the address for k-step s is the
-  // k-step 0 address with bits 5 and 6 XORed by 32 s.
+  uint32_t a_off[G::KS];
   const int r = wm * G::WM + (lane & 31);
-  const uint32_t a_off0 = (uint32_t)(r * TK * 2 + (((lane >> 5) ^ swz_a<TK>(r)) << 4));
-  // B operand: the k-step's 4 x 16 blocks, as in ConsumerOps::load_b, past the A tile.
-  const int grp = lane >> 4;
-  const uint32_t b_off = (uint32_t)(G::A_BYTES +
-                                    ((2 * (grp >> 1)) * G::NQ + (wn * G::WN) / 16 + (grp & 1)) * 128 +
-                                    8 * (lane & 15));
-  static_assert(kHeaderBytes % 128 == 0 && G::STAGE % 128 == 0, "slots on 128-byte boundaries");
+#pragma unroll
+  for (int s = 0; s < G::KS; ++s)
+    a_off[s] = (uint32_t)(r * TK * 2 + (((2 * s + (lane >> 5)) ^ swz_a<TK>(r)) << 4));
+  const uint32_t b_off = G::A_BYTES + b_read_off<TN>(lane, wn * G::WN);
 
   const uint32_t S = (uint32_t)args.iters;
-  if (S % (uint32_t)Loop::kIterQuantum != 0) {
+  if (Loop::kMinIters > 1 && S < (uint32_t)Loop::kMinIters) {
     consumer<TM, TN, TK, NC, NPW, SPLIT, BF16, false, MODE, GENERAL>(args, smem, cw, lane);
     return;
   }
@@ -1399,23 +1481,27 @@ __device__ __forceinline__ void consumer_deep(const KernelArgs& args, WSG_LDS ch
   if (g0 >= args.num_tiles) return;
   const int my_tiles = (args.num_tiles - g0 + Gd - 1) / Gd;
   const uint32_t P = (uint32_t)args.stages;
-  const uint32_t ring = (uint32_t)(uintptr_t)(smem + kHeaderBytes);
-  const uint32_t fullb = (uint32_t)(uintptr_t)full;
-  const uint32_t emptyb = (uint32_t)(uintptr_t)empty;
-  const uint32_t abortb = (uint32_t)(uintptr_t)abort_flag;
+  RingCursor rc;
+  rc.slot = rc.ring = (uint32_t)(uintptr_t)(smem + kHeaderBytes);
+  rc.ring_end = rc.ring + P * (uint32_t)G::STAGE;
+  rc.full = rc.full0 = (uint32_t)(uintptr_t)full;
+  rc.full_end = rc.full0 + 4 * P;
+  rc.empty = rc.empty0 = (uint32_t)(uintptr_t)empty;
+  rc.empty_end = rc.empty0 + 4 * P;
+  rc.abort_flag = (uint32_t)(uintptr_t)abort_flag;
+  rc.target = (uint32_t)G::NP;
 
   int v = g0, ti, tj;
   tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
   f32x16_t acc[BM][BN];
-  uint32_t slot = 0, ftarget = (uint32_t)G::NP;  // K-iteration 0: ring_slot 0, ring_full_target NP
   for (int t = 0; t < my_tiles; ++t) {
 #pragma unroll
     for (int mb = 0; mb < BM; ++mb)
 #pragma unroll
       for (int nb = 0; nb < BN; ++nb) acc[mb][nb] = f32x16_t{};
-    if (!wait_counter(&full[slot], ftarget, abort_flag, args.spin_limit, args.err)) return;
-    const uint32_t st = Loop::tile(acc, a_off0, b_off, slot, ftarget, P, S, ring, fullb, emptyb, abortb,
-                                   args.spin_limit, args.consumer_delay);
+    if (!wait_counter((WSG_LDS uint32_t*)(uintptr_t)rc.full, rc.target, abort_flag, args.spin_limit, args.err))
+      return;
+    const uint32_t st = Loop::tile(acc, a_off, b_off, rc, S, args.spin_limit, args.consumer_delay);
     if (st != 0) {
       if (st == 2) report_timeout(abort_flag, args.err);
       return;
@@ -1423,8 +1509,7 @@ __device__ __forceinline__ void consumer_deep(const KernelArgs& args, WSG_LDS ch
     // The calibration MATH kernel keeps its products (the store below is
     // never taken: M > 0) without writing C.
     if (MODE != kModeMath || args.M < 0)
-      store_tile<TM, TN, G::WM, G::WN, BM, BN, GENERAL, (BN > 2 ? 32 / BN : 16)>(args, acc, ti, tj, wm, wn,
-                                                                                  lane);
+      store_tile<TM, TN, G::WM, G::WN, BM, BN, GENERAL, EG>(args, acc, ti, tj, wm, wn, lane);
     v += Gd;
     tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
   }
@@ -1433,8 +1518,8 @@ __device__ __forceinline__ void consumer_deep(const KernelArgs& args, WSG_LDS ch
 // ---------------------------------------------------------------------------
 // Consumer with two consumer waves per SIMD: the eight-consumer arrangement
 // (2 x 4 grid of 128 x 64 wave tiles next to four producer waves) and the
-// four-consumer 128 x 128 x 32 kernel held to 128 registers a wave (2 x 2
-// grid of 64 x 64 wave tiles, two workgroups per CU).  The K loop of a tile is
+// event-traced four-consumer 128 x 128 x 32 kernel held to 128 registers a wave
+// (2 x 2 grid of 64 x 64 wave tiles, two workgroups per CU).  The K loop of a tile is
 // the generated RollLoop block (ws_deep_loop.inc).  Its fragments are
 // single-buffered and refilled right after their last MFMA of the k-step; the
 // other consumer wave of the SIMD covers the read latency.
@@ -1455,10 +1540,7 @@ __device__ __forceinline__ void consumer_roll(const KernelArgs& args, WSG_LDS ch
   // block moves it to k-step s by XORing 32 s into the byte offset.
   const int r = wm * G::WM + (lane & 31);
   const uint32_t a_off0 = (uint32_t)(r * TK * 2 + (((lane >> 5) ^ swz_a<TK>(r)) << 4));
-  const int grp = lane >> 4;
-  const uint32_t b_off = (uint32_t)(G::A_BYTES +
-                                    ((2 * (grp >> 1)) * G::NQ + (wn * G::WN) / 16 + (grp & 1)) * 128 +
-                                    8 * (lane & 15));
+  const uint32_t b_off = G::A_BYTES + b_read_off<TN>(lane, wn * G::WN);
   static_assert(kHeaderBytes % 128 == 0 && G::STAGE % 128 == 0, "slots on 128-byte boundaries");
 
   const int Gd = gridDim.x;
@@ -1517,8 +1599,9 @@ __device__ __forceinline__ void consumer_roll(const KernelArgs& args, WSG_LDS ch
 }
 
 // ---------------------------------------------------------------------------
-// Register-lean consumer for three waves per SIMD (two producers per consumer
-// with the largest wave tiles): every operand fragment is single-buffered and
+// Compiler-scheduled register-lean consumer for three waves per SIMD (the
+// event-traced twins of the largest four-consumer tiles with eight producer
+// waves): every operand fragment is single-buffered and
 // refilled right after its last MFMA of the k-step, and the loop body is one
 // k-step, so each fragment has a single load site and keeps its registers.
 // Waits and releases are branch-free asm blocks enabled on the last k-step
@@ -1539,9 +1622,7 @@ __device__ __forceinline__ void consumer_rolling(const KernelArgs& args, WSG_LDS
   // in-row byte offset change with s.
   const int r = wm * G::WM + (lane & 31);
   const uint32_t a_off0 = (uint32_t)(r * TK * 2 + (((lane >> 5) ^ swz_a<TK>(r)) << 4));
-  const int grp = lane >> 4;
-  const uint32_t b_off =
-      (uint32_t)(((2 * (grp >> 1)) * G::NQ + (wn * G::WN) / 16 + (grp & 1)) * 128 + 8 * (lane & 15));
+  const uint32_t b_off = b_read_off<TN>(lane, wn * G::WN);
   const uint32_t ring = (uint32_t)(uintptr_t)smem + kHeaderBytes;
 
   const int Gd = gridDim.x;
@@ -1679,11 +1760,11 @@ __device__ __forceinline__ void consumer_release_only(const KernelArgs& args, WS
   const int my_tiles = g0 < args.num_tiles ? (args.num_tiles - g0 + Gd - 1) / Gd : 0;
   const uint32_t total = (uint32_t)my_tiles * (uint32_t)args.iters;
   const uint32_t P = (uint32_t)args.stages;
+  uint32_t slot = 0, target = ring_full_target(0, P, NP);
   for (uint32_t q = 0; q < total; ++q) {
-    const uint32_t slot = ring_slot(q, P);
-    if (!wait_counter(&full[slot], ring_full_target(q, P, NP), abort_flag, args.spin_limit, args.err))
-      return;
+    if (!wait_counter(&full[slot], target, abort_flag, args.spin_limit, args.err)) return;
     lds_signal(&empty[slot]);
+    ring_advance(slot, target, P, NP);
   }
 }
 
@@ -1719,17 +1800,21 @@ __global__ void __launch_bounds__(256) ws_scale_kernel(void* C, int64_t n, float
 template <int UNUSED = 0>
 __global__ void __launch_bounds__(1024) ws_empty_kernel(KernelArgs) {}
 
-// Waves per SIMD a kernel's register allocation must leave room for: the
-// four-consumer roll loop holds its kernel to 128 registers a wave so that two
-// workgroups of eight waves share a CU; every other kernel is sized for one
-// workgroup (what the compiler assumes without the bound).
-template <int TM, int TN, int TK, int NC, int NPW, bool BF16, bool GENERAL>
+// Waves per SIMD a kernel's register allocation must leave room for: what its
+// streaming K loop is laid out for (kVgprs: 256, 168 or 128 registers a wave
+// are two, three or four waves per SIMD; the traced twin of a kernel held to
+// 128 runs the roll loop, laid out for the same), else one workgroup (what the
+// compiler assumes without the bound).
+template <int TM, int TN, int TK, int NC, int NPW, bool BF16, bool TRACE>
 constexpr int kernel_waves_per_simd() {
-  return (NC == 4 && !GENERAL && RollLoop<TM, TN, TK, NC, NPW, BF16>::kAvailable) ? 4 : (NC + NPW + 3) / 4;
+  using Loop = StreamLoop<TM, TN, TK, NC, NPW, BF16>;
+  if (Loop::kAvailable && !TRACE) return 512 / Loop::kVgprs;
+  if (NC == 4 && RollLoop<TM, TN, TK, NC, NPW, BF16>::kAvailable) return 4;
+  return (NC + NPW + 3) / 4;
 }
 
 template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, bool TRACE, int MODE, bool GENERAL>
-__global__ void __launch_bounds__((NC + NPW) * 64, (kernel_waves_per_simd<TM, TN, TK, NC, NPW, BF16, GENERAL>()))
+__global__ void __launch_bounds__((NC + NPW) * 64, (kernel_waves_per_simd<TM, TN, TK, NC, NPW, BF16, TRACE>()))
     ws_gemm_kernel(KernelArgs args) {
   using G = Cfg<TM, TN, TK, NC, NPW, SPLIT, BF16>;
   extern __shared__ __attribute__((aligned(1024))) char smem_generic[];
@@ -1745,24 +1830,19 @@ __global__ void __launch_bounds__((NC + NPW) * 64, (kernel_waves_per_simd<TM, TN
       consumer_release_only<G::NP, NC>(args, smem);
     } else if constexpr (MODE == kModeEpilogue) {
       consumer_epilogue_only<TM, TN, TK, NC, NPW, SPLIT, BF16>(args, wave, lane);
-    } else if constexpr ((!GENERAL || NC == 8) && (MODE == kModeGemm || MODE == kModeMath) &&
-                         RollLoop<TM, TN, TK, NC, NPW, BF16>::kAvailable) {
-      // Two consumer waves per SIMD (eight consumer waves, or four with two
-      // workgroups per CU): the generated register-lean K loop (and its
-      // event-traced twin).  The general variant of the eight-consumer
-      // arrangement runs it too: its producers zero-fill what lies outside A
-      // and B, so the K loop is the plain one, and only the epilogue differs.
+    } else if constexpr (!TRACE && StreamLoop<TM, TN, TK, NC, NPW, BF16>::kAvailable) {
+      // One or four consumer waves: the streaming K loop, in the general
+      // variant too (its producers zero-fill what lies outside A and B, so
+      // only the epilogue differs).
+      consumer_stream<TM, TN, TK, NC, NPW, SPLIT, BF16, MODE, GENERAL>(args, smem, wave, lane);
+    } else if constexpr (RollLoop<TM, TN, TK, NC, NPW, BF16>::kAvailable) {
+      // Two consumer waves per SIMD: the generated register-lean K loop, its
+      // general variant and its event-traced twin.
       consumer_roll<TM, TN, TK, NC, NPW, SPLIT, BF16, TRACE, MODE, GENERAL>(args, smem, wave, lane);
     } else if constexpr (G::NW > 8 && G::BM * G::BN >= 8) {
-      // Three waves per SIMD leave 168 VGPRs: the largest wave tiles then
-      // take the single-buffered consumer.
+      // Traced; three waves per SIMD leave 168 VGPRs: the largest wave tiles
+      // then take the single-buffered consumer.
       consumer_rolling<TM, TN, TK, NC, NPW, SPLIT, BF16, TRACE, MODE, GENERAL>(args, smem, wave, lane);
-    } else if constexpr (!TRACE && (MODE == kModeGemm || MODE == kModeMath) &&
-                         DeepLoop<TM, TN, TK, NC, NPW, BF16>::kAvailable) {
-      // One producer group with the largest tiles (DeepLoop lists them): the
-      // hand-scheduled deep-prefetch K loop, in the general variant too (its
-      // producers zero-fill what lies outside A and B).
-      consumer_deep<TM, TN, TK, NC, NPW, SPLIT, BF16, MODE, GENERAL>(args, smem, wave, lane);
     } else {
       consumer<TM, TN, TK, NC, NPW, SPLIT, BF16, TRACE, MODE, GENERAL>(args, smem, wave, lane);
     }

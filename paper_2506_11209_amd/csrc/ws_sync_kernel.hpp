@@ -58,9 +58,7 @@ __global__ void __launch_bounds__(NC * 64) ws_sync_kernel(KernelArgs args) {
 #pragma unroll
   for (int n = 0; n < G::B_PER; ++n) {
     const int q = (wave + n * NC) * 64 + lane;
-    const int blk = q >> 3, w = q & 7;
-    const int kq = blk / G::NQ, nq = blk % G::NQ;
-    b_goff[n] = (uint32_t)((kq * 4 + (w >> 1)) * N + nq * 16 + (w & 1) * 8) * 2u;
+    b_goff[n] = (uint32_t)(b_chunk_row<TN>(q) * N + b_chunk_col<TN>(q)) * 2u;
   }
   auto issue = [&](int ti, int tj, int kk, int slot) {
     const __amdgpu_buffer_rsrc_t a_src = panel_rsrc(args.A + (int64_t)ti * TM * K + kk * TK);
@@ -83,9 +81,7 @@ __global__ void __launch_bounds__(NC * 64) ws_sync_kernel(KernelArgs args) {
     for (int s = 0; s < G::KS; ++s)
       a_off[s] = (uint32_t)(r * TK * 2 + (((2 * s + (lane >> 5)) ^ swz_a<TK>(r)) << 4));
   }
-  const int grp = lane >> 4;
-  const uint32_t b_off =
-      (uint32_t)(((2 * (grp >> 1)) * G::NQ + (wn * G::WN) / 16 + (grp & 1)) * 128 + 8 * (lane & 15));
+  const uint32_t b_off = b_read_off<TN>(lane, wn * G::WN);
 
   f32x16_t acc[G::BM][G::BN];
   i16x8_t fa[2][G::BM], fb[2][G::BN];
