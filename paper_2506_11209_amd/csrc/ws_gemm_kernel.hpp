@@ -27,7 +27,9 @@
 //  * 1:1 split (NP == NC): every producer loads a share of the A tile and then
 //    a share of the B tile, in that order (one DMA warp loading both tiles).
 //    2:1 split (NP == 2 NC): the first half of the producers loads A, the
-//    second half loads B, concurrently (two DMA warps, one tile each).
+//    second half loads B, concurrently (two DMA warps, one tile each).  With
+//    four consumer waves the waves that load a tile form two groups that take
+//    the K-iterations in turn.
 //  * Consumers read operands with ds_read_b128 (A, K-contiguous) and
 //    ds_read_b64_tr_b16 (B, N-contiguous, transposed by the read) and
 //    accumulate with v_mfma_f32_32x32x16_{bf16,f16} in fp32.  The K loop of a
@@ -790,6 +792,17 @@ struct RingCursor {
 // wave: iteration q is signalled once iteration q + lag has been issued.
 // Before blocking on a slot that is still in use, every pending iteration is
 // published (oldest first), so a consumer never waits on data that landed.
+//
+// GROUPS: the waves that load a tile are split into that many groups; group g
+// takes the K-iterations q with q % GROUPS == g, and each of its waves adds
+// GROUPS to full[], so a use of a slot still counts NP signals.  What bounds a
+// single group is its own chain (wait for the slot, issue, wait for the data,
+// signal): with P = 3 slots it kept one K-iteration in flight while it waited
+// for the landing of the one before.  Two groups run that chain side by side:
+// the load-only kernel of 128x256x32 (2:1, three slots, 4096x8192x2048) went
+// from 134 to 91 us and the GEMM from 168 to 151 us, 128x64x64 (2:1, four
+// slots, 16384x256x8192) from 145 to 112 us, 128x128x32 (three slots, 4096^3)
+// from 165 to 151 us.
 // ---------------------------------------------------------------------------
 
 // Block until at most n of this wave's most recent K-iterations (LOADS DMA
@@ -942,6 +955,16 @@ __device__ __forceinline__ void producer_loop(const KernelArgs& args, WSG_LDS ch
 // worth, independent of the LDS ring depth: producer waves get the kernel's
 // full VGPR allocation (sized for the consumers) and would otherwise leave
 // it idle.  The LDS layout is the one the LDS-DMA producer writes.
+//
+// GROUPS as in producer_loop.  A wave's writes (1 KiB in 13 clocks for the
+// whole CU), its signal and its loads (1 KiB in 16 clocks of the CU's address
+// unit) follow each other, and waves that wait for the same slot do them in
+// step, so the LDS idles while they load and the address unit while they
+// write.  Two groups are in different phases: 128x128x64 (four slots, 4 + 4
+// waves, 2048x2048x32768) took 1161 clocks per K-iteration with one group and
+// 968 with two (292 -> 269 us), 128x128x32 at 4096^3 159 -> 156 us, 128x256x32
+// (four slots) 134.6 -> 129.6 us, 128x64x64 2:1 (16384x256x8192)
+// 111 -> 103 us; its general twin, whose loads test their chunks, 122 -> 109.
 // ---------------------------------------------------------------------------
 template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, bool TRACE, bool DO_A, bool DO_B,
           bool GENERAL, int GROUPS>
@@ -1214,8 +1237,14 @@ template <int TM, int TN, int TK, int NC, int NPW, int SPLIT, bool BF16, bool ST
           bool GENERAL>
 __device__ __forceinline__ void producer_run(const KernelArgs& args, WSG_LDS char* smem, int a_rank, int b_rank,
                                              int lane) {
-  constexpr int GR = 1;
-  constexpr int GD = 1;
+  // Producer groups (see producer_loop_reg).  One where a wave group cannot be
+  // halved (one consumer wave), where a stamp stands for every K-iteration
+  // (tracing), and on the register path of the eight-consumer arrangement:
+  // there a group of two waves could stage only one K-iteration, and the two
+  // ring slots leave one free at a time (256x256x64 at 8192^3: 838 us with one
+  // group, 852 with two; its LDS-DMA path gains 0-2 %).
+  constexpr int GR = (STAMP || NC != 4) ? 1 : 2;
+  constexpr int GD = (STAMP || NC == 1) ? 1 : 2;
   if constexpr (GENERAL) {  // partial tiles possible: always register-staged
     producer_loop_reg<TM, TN, TK, NC, NPW, SPLIT, BF16, STAMP, DO_A, DO_B, true, GR>(args, smem, a_rank, b_rank,
                                                                                 lane);
