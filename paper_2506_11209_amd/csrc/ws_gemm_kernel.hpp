@@ -55,10 +55,17 @@
 //   [256 + s * STAGE)   slot s: A tile (TM x TK) then B tile (TK x TN)
 // A tile: row-major, each row split in 16-byte chunks (8 elements); chunk c of
 //   row r is stored at position c ^ swz_a(r).
-// B tile: 4 x 16 element blocks of 128 bytes; block (kq, nq) holds rows
-//   4 kq .. 4 kq + 3 and columns 16 nq .. 16 nq + 15, row-major inside the
-//   block; blocks are ordered kq-major.  One 16-lane transposed read takes one
-//   whole block.
+// B tile: 4 x 32 element blocks of 256 bytes; block (kq, nd) holds rows
+//   4 kq .. 4 kq + 3 and columns 32 nd .. 32 nd + 31, row-major inside the
+//   block (64 bytes a row); blocks are ordered kq-major.  A 16-lane
+//   transposed read takes one 16-column half of a block (32 bytes of each
+//   row), two neighbouring groups the whole block.  Why 32 columns: chunk q
+//   goes to byte 16 q of the tile on every load path, so four neighbouring
+//   lanes fetch the 64 bytes of one block row.  The address unit takes four
+//   16-byte lanes per clock when they lie in one cache line and twice as long
+//   when they do not: with 16-column blocks (two rows per four lanes) B loads
+//   ran at 31.9 bytes per clock and CU, with these at 63.8, the rate of the A
+//   loads and of linear ones (L2-resident panel, one workgroup per CU).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -196,11 +203,11 @@ constexpr bool swz_a_step_invariant(int step) {
 // stored at byte 16 q.
 template <int TN>
 __host__ __device__ constexpr int b_chunk_row(int q) {
-  return (q >> 3) / (TN / 16) * 4 + ((q & 7) >> 1);
+  return (q >> 4) / (TN / 32) * 4 + ((q >> 2) & 3);
 }
 template <int TN>
 __host__ __device__ constexpr int b_chunk_col(int q) {
-  return (q >> 3) % (TN / 16) * 16 + (q & 1) * 8;
+  return (q >> 4) % (TN / 32) * 32 + (q & 3) * 8;
 }
 
 // Byte offset, inside the B tile, of a lane's transposed 8-byte read of
@@ -210,7 +217,7 @@ __host__ __device__ constexpr int b_chunk_col(int q) {
 template <int TN>
 __host__ __device__ constexpr uint32_t b_read_off(int lane, int col) {
   const int g = lane >> 4, j = lane & 15;
-  return (uint32_t)(((2 * (g >> 1)) * (TN / 32) + col / 32) * 256 + (g & 1) * 128 + j * 8);
+  return (uint32_t)(((2 * (g >> 1)) * (TN / 32) + col / 32) * 256 + (j >> 2) * 64 + (g & 1) * 32 + (j & 3) * 8);
 }
 
 // Every read lands on the chunk that holds its row and columns.

@@ -53,8 +53,8 @@ def swz_a(tk, r):
 
 class Lane:
     """A lane's operand addresses: A rows of TK elements in 16-byte chunks,
-    chunk k of row r at position k ^ swz(r); B in 4 x 16 blocks of 128 bytes,
-    32 bytes a row.  Lane l of an A read takes row l % 32, chunk l / 32 of the
+    chunk k of row r at position k ^ swz(r); B in 4 x 32 blocks of 256 bytes,
+    64 bytes a row.  Lane l of an A read takes row l % 32, chunk l / 32 of the
     k-step; 16-lane group g of a B read takes k-rows 8 (g / 2) .. + 3 (and + 4)
     and column half g % 2, four lanes to a row."""
 
@@ -72,8 +72,8 @@ class Lane:
 
     def b_byte(self, kss, nb, half):
         k, col = 16 * kss + self.krow + 4 * half, self.col0 + 32 * nb
-        block = (k // 4) * (self.c.tn // 16) + col // 16
-        return self.c.a_bytes + 128 * block + 32 * (k % 4) + 2 * (col % 16)
+        block = (k // 4) * (self.c.tn // 32) + col // 32
+        return self.c.a_bytes + 256 * block + 64 * (k % 4) + 2 * (col % 32)
 
 
 def vregs(tok):
