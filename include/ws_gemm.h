@@ -25,6 +25,14 @@
  * `stages` is the circular buffer's capacity in K-iterations (the buffer of
  * Section 2.2 holding at most a fixed number of tiles).
  *
+ * Tile parts: when the output has too few tiles to fill the GPU, the library
+ * may compute each tile in parts by several workgroups of the same wave
+ * arrangement (four consumer waves for parts of a 256 x 256 tile), with the
+ * ring's bytes shared out over more, smaller K-iterations.  Results are the
+ * same to the bit (every element takes its products in the same order), and
+ * the plan a handle reports stays that of its whole tiles; calibration
+ * kernels take the parts of the GEMM they calibrate, traced runs whole tiles.
+ *
  * Data layout: A, B and C are dense and row-major (leading dimensions K, N
  * and N).  A and B hold IEEE binary16 (WS_F16) or bfloat16 (WS_BF16)
  * elements; C is binary32 unless an epilogue says otherwise.  Products are
@@ -192,7 +200,7 @@ ws_status ws_gemm_sync_status(ws_gemm_t h, hipStream_t stream);
 ws_status ws_gemm_clock(ws_gemm_t h, hipStream_t stream, uint64_t* shader_cycles,
                         uint64_t* ref_ticks, int64_t* launches);
 
-/* The plan a handle launches with. */
+/* The plan a handle launches with (of whole tiles, see "Tile parts" above). */
 ws_status ws_gemm_query(ws_gemm_t h, ws_gemm_plan_info* out);
 
 /* Epilogue of later runs (NULL restores the default).  A non-default

@@ -114,6 +114,178 @@ wsg::PlanIn plan_in(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, in
   return in;
 }
 
+// A kernel and the grid it is launched with; corner_m >= 0: of the plan's tiles
+// only those outside the block of the first corner_m rows and corner_n columns.
+struct Launch {
+  const void* fn;
+  wsg::PlanOut plan;
+  int32_t stages;
+  int32_t corner_m, corner_n;
+};
+// What one run launches, in stream order.
+struct Run {
+  Launch launch[2];
+  int count;
+};
+
+int64_t tiles_of(int64_t M, int64_t N, const ws_gemm_config& k) {
+  return ((M + k.tile_m - 1) / k.tile_m) * ((N + k.tile_n - 1) / k.tile_n);
+}
+
+// The configuration of a part of a tile of c: the same T_K, dtype and split
+// (four consumer waves for parts of the eight-consumer 256 x 256 tile).
+ws_gemm_config part_of(const ws_gemm_config& c, int tm, int tn) {
+  ws_gemm_config k = c;
+  k.tile_m = tm;
+  k.tile_n = tn;
+  k.split = split_of(c);
+  if (c.consumer_waves == 8 && (tm < c.tile_m || tn < c.tile_n)) k.consumer_waves = 4;
+  return k;
+}
+
+// Calls f(config, cost) for every compiled part of c's tile (the whole tile
+// left out) that is cheaper than `limit`: `count(config)` tiles of it.
+template <typename Count, typename F>
+void each_part(const ws_gemm_config& c, int cus, int mode, int general, int64_t limit, Count count, F f) {
+  const int least = c.consumer_waves == 1 ? 32 : 64;
+  for (int tm = c.tile_m; tm >= least; tm /= 2)
+    for (int tn = c.tile_n; tn >= least; tn /= 2) {
+      if (tm == c.tile_m && tn == c.tile_n) continue;
+      const ws_gemm_config k = part_of(c, tm, tn);
+      const int64_t cost = wsg::tiles_cost(count(k), tm, tn, cus);
+      if (cost < limit && find_kernel(k, 0, mode, general)) {
+        f(k, cost);
+        limit = cost;
+      }
+    }
+}
+
+// Workgroups of k's kernel that a CU runs when there are `tiles` of them.
+int per_cu(const ws_gemm_config& k, int64_t tiles, int cus) {
+  int v = 0, a = 0;
+  kernel_regs(k, &v, &a);
+  const int waves = k.consumer_waves + k.producer_waves;
+  const int64_t fit = 4 * wsg::waves_per_simd_by_regs(v, a) / waves, want = (tiles + cus - 1) / cus;
+  return (int)(want < fit ? want : fit);
+}
+
+// Plan of `tiles` tiles of part k of c on the M x N x K problem.
+bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm_config k, int64_t tiles, int cus,
+               int mode, int general, Launch* l) {
+  k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n), 2ll * c.tile_k * (k.tile_m + k.tile_n),
+                              per_cu(k, tiles, cus));
+  if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0), &l->plan) != wsg::kPlanOk) return false;
+  l->fn = find_kernel(k, 0, mode, general)->fn;
+  l->stages = k.stages;
+  l->corner_m = l->corner_n = -1;
+  return true;
+}
+
+// Chooses how to compute the problem with the kernel (mode, general) of c:
+// whole tiles (as `out` comes in), every tile in parts, or a block of whole
+// tiles and, in a second launch, the rest in parts - the rest being partial
+// edge tiles, which would multiply padding for a round of their own, or what a
+// nearly empty last round would take.  plain_block: the block's tiles may run
+// the plain kernel (default epilogue; they are whole).  Specialised kernels
+// only: the synchronous one is the baseline at its tile.
+//
+// Measured, whole tiles -> block and rest: 4100x4104x4104 with 256x256x64 tiles
+// (289 tiles, 33 of them almost all padding) 199 -> 148 us, as 128x128 parts
+// 269 us.
+ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int mode, int general,
+                     bool plain_block, Run* out) {
+  if (c.producer_waves == 0) return WS_OK;
+  const Launch& whole = out->launch[0];
+  // costs of the whole problem: part_cost units are ns per 64 of K
+  const int64_t slabs = (K + 63) / 64;
+  const int64_t whole_cost = wsg::tiles_cost(whole.plan.tiles, c.tile_m, c.tile_n, cus) * slabs;
+  int64_t best = whole_cost * 10 / 11;  // what another partition must not exceed
+  ws_gemm_config part{}, rest{};
+  each_part(c, cus, mode, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
+            [&](const ws_gemm_config& k, int64_t cost) {
+              part = k;
+              best = cost * slabs;
+            });
+  int rows_best = 0, cols_best = 0;
+  if (mode == wsg::kModeGemm) {
+    const int64_t rows = M / c.tile_m, cols = N / c.tile_n, rounds = rows * cols / cus;
+    for (int t = 0; t < 3 && rows > 0 && cols > 0; ++t) {
+      // all whole tiles, or as many rows (columns) of them as whole rounds hold
+      const int64_t r = t == 1 ? rounds * cus / cols : rows, q = t == 2 ? rounds * cus / rows : cols;
+      if (r < 1 || q < 1 || (r * c.tile_m >= M && q * c.tile_n >= N)) continue;
+      const int64_t block = wsg::tiles_cost(r * q, c.tile_m, c.tile_n, cus) * slabs + wsg::kSecondLaunchNs;
+      if (block >= best) continue;
+      each_part(c, cus, mode, general, (best - block) / slabs,
+                [&](const ws_gemm_config& k) {
+                  return tiles_of(M, N, k) - r * q * (c.tile_m / k.tile_m) * (c.tile_n / k.tile_n);
+                },
+                [&](const ws_gemm_config& k, int64_t cost) {
+                  rest = k;
+                  rows_best = (int)r;
+                  cols_best = (int)q;
+                  best = block + cost * slabs;
+                });
+    }
+  }
+  Run run = *out;
+  if (rows_best > 0) {
+    run.count = 2;
+    Launch& m = run.launch[0];
+    Launch& e = run.launch[1];
+    if (wsg::plan_launch(plan_in((int64_t)rows_best * c.tile_m, (int64_t)cols_best * c.tile_n, K, c, cus, 0),
+                         &m.plan) != wsg::kPlanOk)
+      return WS_OK;
+    const wsg::KernelEntry* plain = plain_block && K % c.tile_k == 0 ? find_kernel(c, 0, mode, 0) : nullptr;
+    if (plain) m.fn = plain->fn;
+    const int cm = rows_best * (c.tile_m / rest.tile_m), cn = cols_best * (c.tile_n / rest.tile_n);
+    const int64_t tiles = tiles_of(M, N, rest) - (int64_t)cm * cn;
+    if (!plan_part(M, N, K, c, rest, tiles, cus, mode, general, &e)) return WS_OK;
+    e.corner_m = cm;
+    e.corner_n = cn;
+    e.plan.tiles = (int32_t)tiles;
+    if (tiles < e.plan.grid) e.plan.grid = (int32_t)tiles;
+    e.plan.rounds = (int32_t)((tiles + e.plan.grid - 1) / e.plan.grid);
+    e.plan.xcd_remap = e.plan.grid % 8 == 0;
+  } else if (part.tile_m > 0) {
+    if (!plan_part(M, N, K, c, part, tiles_of(M, N, part), cus, mode, general, &run.launch[0])) return WS_OK;
+  } else {
+    return WS_OK;
+  }
+  for (int i = 0; i < run.count; ++i)
+    WSG_HIP(hipFuncSetAttribute(run.launch[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                run.launch[i].plan.lds_bytes));
+  *out = run;
+  return WS_OK;
+}
+
+// Enqueues a run; `a` has everything but what a launch decides.
+ws_status launch_run(const Run& run, wsg::KernelArgs a, hipStream_t stream) {
+  for (int i = 0; i < run.count; ++i) {
+    const Launch& l = run.launch[i];
+    a.tiles_m = l.plan.tiles_m;
+    a.tiles_n = l.plan.tiles_n;
+    a.num_tiles = l.plan.tiles;
+    a.iters = l.plan.iters;
+    a.stages = l.stages;
+    a.group_m = l.plan.group_m;
+    a.xcd_remap = l.plan.xcd_remap;
+    a.region2 = INT32_MAX;
+    a.row1 = a.tiles2_m = a.tiles2_n = a.col2 = 0;
+    if (l.corner_m >= 0) {  // the rows below the block, then the columns right of it, down the rows first
+      a.row1 = l.corner_m;
+      a.tiles_m = a.group_m = l.plan.tiles_m - l.corner_m;
+      a.region2 = a.tiles_m * l.plan.tiles_n;
+      a.tiles2_m = l.corner_m;
+      a.tiles2_n = l.plan.tiles_n - l.corner_n;
+      a.col2 = l.corner_n;
+    }
+    if (i > 0) a.clock = nullptr;  // one clock sample per run, of its main launch
+    void* params[] = {&a};
+    WSG_HIP(hipLaunchKernel(l.fn, dim3(l.plan.grid), dim3(l.plan.block), params, (size_t)l.plan.lds_bytes, stream));
+  }
+  return WS_OK;
+}
+
 void to_info(const wsg::PlanOut& p, ws_gemm_plan_info* o) {
   o->grid = p.grid;
   o->block = p.block;
@@ -187,8 +359,9 @@ struct ws_gemm_handle {
   const wsg::KernelEntry* kernel;
   const wsg::KernelEntry* traced;  // instrumented variant (null if none was compiled)
   const wsg::KernelEntry* general; // general twin (partial tiles, epilogue options), or null
-  const void* launch_fn;           // kernel launched by ws_gemm_run when not tracing
-  wsg::PlanOut plan_plain, plan_general;  // launches of the plain and the general kernel
+  wsg::PlanOut plan_plain, plan_general;  // whole-tile plans of the plain and the general kernel
+  Run run_plain, run_general;      // what ws_gemm_run launches for the default / another epilogue
+  bool use_general;                // another epilogue is set
   ws_gemm_epilogue epi;
   bool calibration;
   int device;
@@ -309,6 +482,18 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
       general = nullptr;
   }
 
+  // Empty problems launch no GEMM kernel.
+  Run run_plain{{{launch_fn, p, cfg->stages, -1, -1}, {}}, 1};
+  Run run_general{{{general ? general->fn : nullptr, pg, cfg->stages, -1, -1}, {}}, 1};
+  if (p.grid > 0) {
+    const int mode = kind == WS_CALIB_NONE || kind == WS_CALIB_EMPTY ? wsg::kModeGemm : run->mode;
+    ws_status ls = kind == WS_CALIB_EMPTY ? WS_OK
+                                          : choose_run(M, N, K, *cfg, cus, mode, p.ragged, true, &run_plain);
+    if (ls == WS_OK && general)
+      ls = choose_run(M, N, K, *cfg, cus, wsg::kModeGemm, 1, false, &run_general);
+    if (ls != WS_OK) return ls;
+  }
+
   ws_gemm_handle* h = new (std::nothrow) ws_gemm_handle();
   if (!h) return WS_ERR_INVALID_ARG;
   h->M = M;
@@ -317,10 +502,12 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   h->cfg = *cfg;
   h->plan = p;
   h->kernel = run;
-  h->launch_fn = launch_fn;
   h->general = general;
   h->plan_plain = p;
   h->plan_general = pg;
+  h->run_plain = run_plain;
+  h->run_general = run_general;
+  h->use_general = false;
   h->epi = ws_gemm_epilogue{1.0f, 0.0f, WS_OUT_F32};
   h->calibration = kind != WS_CALIB_NONE;
   h->traced = (kind == WS_CALIB_NONE && !p.ragged) ? find_kernel(*cfg, 1) : nullptr;
@@ -396,13 +583,6 @@ ws_status ws_gemm_run(ws_gemm_t h, const void* A, const void* B, void* C, hipStr
   a.M = (int32_t)h->M;
   a.N = (int32_t)h->N;
   a.K = (int32_t)h->K;
-  a.tiles_m = h->plan.tiles_m;
-  a.tiles_n = h->plan.tiles_n;
-  a.num_tiles = h->plan.tiles;
-  a.iters = h->plan.iters;
-  a.stages = h->cfg.stages;
-  a.group_m = h->plan.group_m;
-  a.xcd_remap = h->plan.xcd_remap;
   a.spin_limit = h->dbg.spin_limit > 0 ? h->dbg.spin_limit : kDefaultSpinLimit;
   a.producer_delay = h->dbg.producer_delay;
   a.consumer_delay = h->dbg.consumer_delay;
@@ -415,11 +595,10 @@ ws_status ws_gemm_run(ws_gemm_t h, const void* A, const void* B, void* C, hipStr
   a.beta = h->epi.beta;
   a.out_dtype = h->epi.out_dtype;
   a.clock = (unsigned long long*)((char*)h->d_err + kClockOffset);
-  void* params[] = {&a};
-  const void* fn = (h->trace && h->traced) ? h->traced->fn : h->launch_fn;
-  WSG_HIP(hipLaunchKernel(fn, dim3(h->plan.grid), dim3(h->plan.block), params,
-                          (size_t)h->plan.lds_bytes, stream));
-  return WS_OK;
+  // the traced twin runs the whole-tile plan, which its records describe
+  if (h->trace && h->traced)
+    return launch_run(Run{{{h->traced->fn, h->plan, h->cfg.stages, -1, -1}, {}}, 1}, a, stream);
+  return launch_run(h->use_general ? h->run_general : h->run_plain, a, stream);
 }
 
 ws_status ws_gemm_sync_status(ws_gemm_t h, hipStream_t stream) {
@@ -451,7 +630,7 @@ ws_status ws_gemm_clock(ws_gemm_t h, hipStream_t stream, uint64_t* shader_cycles
 ws_status ws_gemm_query(ws_gemm_t h, ws_gemm_plan_info* out) {
   if (!h || !out) return WS_ERR_INVALID_ARG;
   to_info(h->plan, out);
-  out->general = (h->general && h->launch_fn == h->general->fn) ? 1 : 0;
+  out->general = (h->use_general || h->plan.ragged) ? 1 : 0;
   return WS_OK;
 }
 
@@ -468,18 +647,19 @@ ws_status ws_gemm_set_epilogue(ws_gemm_t h, const ws_gemm_epilogue* epi) {
   // epilogue.
   if (h->plan_plain.grid == 0 || h->plan_plain.ragged) {
     h->epi = e;
+    h->use_general = !dflt;
     return WS_OK;
   }
   if (dflt) {
     h->epi = e;
-    h->launch_fn = h->kernel->fn;
+    h->use_general = false;
     h->plan = h->plan_plain;
     return WS_OK;
   }
   if (!h->general) return WS_ERR_UNSUPPORTED;
   if (h->trace) return WS_ERR_UNSUPPORTED;  // the traced twin has the plain epilogue
   h->epi = e;
-  h->launch_fn = h->general->fn;
+  h->use_general = true;
   h->plan = h->plan_general;
   return WS_OK;
 }
@@ -567,6 +747,9 @@ ws_status ws_gemm_run_noalloc(int64_t M, int64_t N, int64_t K, const ws_gemm_con
   if (occ < 1) return WS_ERR_UNSUPPORTED;
   s = wsg::plan_launch(plan_in(M, N, K, *cfg, sd.cus, occ), &p);
   if (s != wsg::kPlanOk) return from_plan(s);
+  Run run{{{k->fn, p, cfg->stages, -1, -1}, {}}, 1};
+  const ws_status ls = choose_run(M, N, K, *cfg, sd.cus, wsg::kModeGemm, p.ragged, true, &run);
+  if (ls != WS_OK) return ls;
   wsg::KernelArgs a{};
   a.A = (const uint16_t*)A;
   a.B = (const uint16_t*)B;
@@ -574,22 +757,13 @@ ws_status ws_gemm_run_noalloc(int64_t M, int64_t N, int64_t K, const ws_gemm_con
   a.M = (int32_t)M;
   a.N = (int32_t)N;
   a.K = (int32_t)K;
-  a.tiles_m = p.tiles_m;
-  a.tiles_n = p.tiles_n;
-  a.num_tiles = p.tiles;
-  a.iters = p.iters;
-  a.stages = cfg->stages;
-  a.group_m = p.group_m;
-  a.xcd_remap = p.xcd_remap;
   a.spin_limit = kDefaultSpinLimit;
   a.err = (int32_t*)sd.scratch;  // this device's copy of the scratch array
   a.load_path = cfg->load_path;
   a.alpha = 1.0f;
   a.beta = 0.0f;
   a.out_dtype = WS_OUT_F32;
-  void* params[] = {&a};
-  WSG_HIP(hipLaunchKernel(k->fn, dim3(p.grid), dim3(p.block), params, (size_t)p.lds_bytes, stream));
-  return WS_OK;
+  return launch_run(run, a, stream);
 }
 
 }  // extern "C"

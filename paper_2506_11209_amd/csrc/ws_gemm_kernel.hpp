@@ -113,6 +113,11 @@ struct KernelArgs {
   // cycles and the 100 MHz reference ticks it spans to clock[0] and clock[1],
   // and 1 to clock[2]; their ratio is the average shader clock of the launch.
   unsigned long long* clock;
+  // Second tile region: schedule indices from region2 on walk tiles2_m x
+  // tiles2_n tiles whose first column is col2; the ones before walk the first
+  // region (tiles_m, tiles_n, group_m), whose first row is row1.  One region:
+  // region2 is past every index and row1 is 0.
+  int32_t region2, row1, tiles2_m, tiles2_n, col2;
 };
 
 // Output element type of the general variant's epilogue.
@@ -701,6 +706,13 @@ __device__ __forceinline__ void store_tile(const KernelArgs& args, const f32x16_
 // ---------------------------------------------------------------------------
 // Per-workgroup tile sequence (identical in both roles).
 // ---------------------------------------------------------------------------
+__device__ __forceinline__ void tile_at(const KernelArgs& args, int v, int* ti, int* tj) {
+  const bool second = v >= args.region2;
+  tile_coords(second ? v - args.region2 : v, second ? args.tiles2_m : args.tiles_m,
+              second ? args.tiles2_n : args.tiles_n, second ? args.tiles2_m : args.group_m, ti, tj);
+  *ti += second ? 0 : args.row1;
+  *tj += second ? args.col2 : 0;
+}
 __device__ __forceinline__ int first_slot(const KernelArgs& args) {
   const int G = gridDim.x;
   return args.xcd_remap ? xcd_slot(blockIdx.x, G) : (int)blockIdx.x;
@@ -900,7 +912,7 @@ __device__ __forceinline__ void producer_loop(const KernelArgs& args, WSG_LDS ch
       continue;
     }
     int ti, tj;
-    tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+    tile_at(args, v, &ti, &tj);
     const uint16_t* a_tile = args.A + (int64_t)ti * TM * K;
     const uint16_t* b_tile = args.B + (int64_t)tj * TN;
     for (; kk < S; kk += GROUPS, q += GROUPS) {
@@ -1059,7 +1071,7 @@ __device__ __forceinline__ void producer_loop_reg(const KernelArgs& args, WSG_LD
   const char* b_src = nullptr;
   const int64_t a_adv = (int64_t)TK * 2 * GROUPS, b_adv = (int64_t)TK * 2 * GROUPS * N;
   auto point = [&]() {
-    tile_coords(v_i, args.tiles_m, args.tiles_n, args.group_m, &ti_i, &tj_i);
+    tile_at(args, v_i, &ti_i, &tj_i);
     a_src = (const char*)(args.A + (int64_t)ti_i * TM * K + kk_i * TK);
     b_src = (const char*)(args.B + (int64_t)kk_i * TK * N + (int64_t)tj_i * TN);
   };
@@ -1361,7 +1373,7 @@ __device__ __forceinline__ void consumer(const KernelArgs& args, WSG_LDS char* s
 
   int v = g0;
   int ti, tj;
-  tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+  tile_at(args, v, &ti, &tj);
 
   f32x16_t acc[G::BM][G::BN];
 #pragma unroll
@@ -1462,7 +1474,7 @@ __device__ __forceinline__ void consumer(const KernelArgs& args, WSG_LDS char* s
       if (!has_next) break;
       kk = 0;
       v += Gd;
-      tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+      tile_at(args, v, &ti, &tj);
 #pragma unroll
       for (int mb = 0; mb < G::BM; ++mb)
 #pragma unroll
@@ -1528,7 +1540,7 @@ __device__ __forceinline__ void consumer_stream(const KernelArgs& args, WSG_LDS 
   rc.target = (uint32_t)G::NP;
 
   int v = g0, ti, tj;
-  tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+  tile_at(args, v, &ti, &tj);
   f32x16_t acc[BM][BN];
   for (int t = 0; t < my_tiles; ++t) {
 #pragma unroll
@@ -1547,7 +1559,7 @@ __device__ __forceinline__ void consumer_stream(const KernelArgs& args, WSG_LDS 
     if (MODE != kModeMath || args.M < 0)
       store_tile<TM, TN, G::WM, G::WN, BM, BN, GENERAL, EG>(args, acc, ti, tj, wm, wn, lane);
     v += Gd;
-    tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+    tile_at(args, v, &ti, &tj);
   }
 }
 
@@ -1600,7 +1612,7 @@ __device__ __forceinline__ void consumer_roll(const KernelArgs& args, WSG_LDS ch
   };
 
   int v = g0, ti, tj;
-  tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+  tile_at(args, v, &ti, &tj);
   f32x16_t acc[BM][BN];
   uint32_t slot = 0, ftarget = (uint32_t)G::NP;  // K-iteration 0: ring_slot 0, ring_full_target NP
   for (int t = 0; t < my_tiles; ++t) {
@@ -1630,7 +1642,7 @@ __device__ __forceinline__ void consumer_roll(const KernelArgs& args, WSG_LDS ch
       store_tile<TM, TN, G::WM, G::WN, BM, BN, GENERAL, 1>(args, acc, ti, tj, wm, wn, lane);
     if (tracing) record(q0 + S - 1, 7, cycles32());
     v += Gd;
-    tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+    tile_at(args, v, &ti, &tj);
   }
 }
 
@@ -1671,7 +1683,7 @@ __device__ __forceinline__ void consumer_rolling(const KernelArgs& args, WSG_LDS
 
   int v = g0;
   int ti, tj;
-  tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+  tile_at(args, v, &ti, &tj);
 
   f32x16_t acc[G::BM][G::BN];
 #pragma unroll
@@ -1773,7 +1785,7 @@ __device__ __forceinline__ void consumer_rolling(const KernelArgs& args, WSG_LDS
       if (!has_next) break;
       kk = 0;
       v += Gd;
-      tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+      tile_at(args, v, &ti, &tj);
 #pragma unroll
       for (int mb = 0; mb < G::BM; ++mb)
 #pragma unroll
@@ -1815,7 +1827,7 @@ __device__ __forceinline__ void consumer_epilogue_only(const KernelArgs& args, i
     for (int nb = 0; nb < G::BN; ++nb) acc[mb][nb] = f32x16_t{};
   for (int v = first_slot(args); v < args.num_tiles; v += (int)gridDim.x) {
     int ti, tj;
-    tile_coords(v, args.tiles_m, args.tiles_n, args.group_m, &ti, &tj);
+    tile_at(args, v, &ti, &tj);
     store_tile<TM, TN, G::WM, G::WN, G::BM, G::BN>(args, acc, ti, tj, wm, wn, lane);
   }
 }

@@ -215,6 +215,48 @@ inline int plan_launch(const PlanIn& in, PlanOut* out) {
   return kPlanOk;
 }
 
+// Tile parts.  When a problem has too few output tiles to fill the GPU, a tile
+// is computed in parts by several workgroups, each running the kernel compiled
+// for the part's size with the same T_K and producer split.  Every output
+// element still takes its K-steps of 16 in the same order in one accumulator,
+// so the result is the same to the bit; a part loads more operand bytes per
+// product, which the rule below weighs against the idle CUs.
+//
+// Cost of 64 of K on one tile of TM x TN (ns per CU; workgroups that share a
+// CU take turns), from full launches of 4 + 4 waves at T_K = 64, measured /
+// this line: 64x64 260 / 248, 128x64 400 / 367, 128x128 520 / 559,
+// 256x128 900 / 941, 256x256 (8 + 4 waves) 1670 / 1611.
+inline int64_t part_cost(int tm, int tn) {
+  return 80 + (int64_t)tm * tn * 175 / 10000 + 3 * (tm + tn) / 4;
+}
+
+// Time of `tiles` tiles, in part_cost units per 64 of K.
+inline int64_t tiles_cost(int64_t tiles, int tm, int tn, int num_cus) {
+  return (tiles + num_cus - 1) / num_cus * part_cost(tm, tn);
+}
+
+// Another partition must beat whole tiles by a tenth (the line above is good to
+// 7 %).  Measured, whole tiles -> parts: 1024^3 with 128x128x64 tiles (64 tiles,
+// three slots) 11.8 us -> 7.2 us as 64x64 parts, the same with K = 8192 62 -> 32
+// us; 2048x2048x4096 with 256x256x64 tiles (64 tiles) 80 -> 39 us as 128x128
+// parts; 256^3 with 64x64x32 tiles of one consumer wave 7.2 -> 4.9 us as 32x32
+// parts.
+inline bool partition_pays(int64_t cost, int64_t whole) { return cost * 11 <= whole * 10; }
+
+// What a second launch on the stream adds (ns): the first one's drain and the
+// second one's start.
+constexpr int64_t kSecondLaunchNs = 4000;
+
+// Ring slots of a part's kernel: the bytes of the requested ring shared by the
+// workgroups that a CU runs (64x64x64 parts of 1024^3, one per CU: three slots
+// 8.7 us, the six that fill the ring of the 128x128 tiles 7.2 us), at least the
+// requested depth.
+inline int part_stages(int stages, int64_t stage_whole, int64_t stage_part, int per_cu) {
+  const int64_t fit = (int64_t)stages * stage_whole / stage_part / (per_cu < 1 ? 1 : per_cu);
+  const int p = fit < kPlanMaxStages ? (int)fit : kPlanMaxStages;
+  return p < stages ? stages : p;
+}
+
 // Output tile computed by workgroup g in dispatch round r of a plan
 // (returns false when that workgroup has no tile in that round).
 inline bool scheduled_tile(const PlanOut& p, int g, int r, int* ti, int* tj) {
