@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <atomic>
 #include <mutex>
 #include <new>
 
@@ -59,42 +60,76 @@ int split_of(const ws_gemm_config& c) {
   return wsg::arrangement_split(c.consumer_waves, c.producer_waves, c.split);
 }
 
-const wsg::KernelEntry* find_kernel(const ws_gemm_config& c, int trace = 0, int mode = wsg::kModeGemm,
-                                   int general = 0) {
-  const int split = split_of(c);
-  for (int t = 0; t < kNumTables; ++t)
-    for (int i = 0; i < kAllTables[t].count; ++i) {
-      const wsg::KernelEntry& e = kAllTables[t].entries[i];
-      if (e.tm == c.tile_m && e.tn == c.tile_n && e.tk == c.tile_k && e.nc == c.consumer_waves &&
-          e.np == c.producer_waves && e.split == split && e.bf16 == (c.dtype == WS_BF16 ? 1 : 0) &&
-          e.trace == trace && e.mode == mode && e.general == general)
-        return &e;
-    }
-  return nullptr;
-}
-
 #include "ws_gemm_resources.inc"
 
-// Registers per wave of the GEMM kernel of c (0, 0 if not in the table); the
-// kernel for whole tiles stands for its general twin.
-void kernel_regs(const ws_gemm_config& c, int* vgprs, int* agprs) {
-  *vgprs = 0;
-  *agprs = 0;
-  const int split = split_of(c);
-  for (int i = 0; i < kNumResources; ++i) {
-    const wsg::KernelResources& r = kResources[i];
-    if (r.tm == c.tile_m && r.tn == c.tile_n && r.tk == c.tile_k && r.nc == c.consumer_waves &&
-        r.np == c.producer_waves && r.split == split && r.bf16 == (c.dtype == WS_BF16 ? 1 : 0) &&
-        r.trace == 0 && r.mode == 0 && r.general == 0) {
-      *vgprs = r.vgprs;
-      *agprs = r.agprs;
-      return;
+// The compiled kernels by configuration: position in `table` of the key below,
+// built once.  A call of ws_gemm_run_noalloc looks several kernels up (walking
+// the tables took 1 us a call).
+struct KernelIndex {
+  static constexpr int kKeys = 4 * 4 * 3 * 3 * 5 * 3 * 2 * 2 * 6 * 2;
+  struct Slot {
+    const wsg::KernelEntry* kernel;
+    int16_t vgprs, agprs;
+  };
+  Slot slots[1024];
+  int16_t at[kKeys];  // index into slots, -1: not compiled
+  int count = 0;
+
+  static int log2_of(int x, int lo, int hi) {  // position of x among the powers of two lo .. hi, -1 if it is none
+    for (int i = 0, p = lo; p <= hi; ++i, p *= 2)
+      if (p == x) return i;
+    return -1;
+  }
+  static int key(int tm, int tn, int tk, int nc, int np, int split, int bf16, int trace, int mode, int general) {
+    const int a = log2_of(tm, 32, 256), b = log2_of(tn, 32, 256), c = log2_of(tk, 32, 128);
+    const int d = nc == 1 ? 0 : nc == 4 ? 1 : nc == 8 ? 2 : -1;
+    const int e = np == 0 ? 0 : log2_of(np, 1, 8) < 0 ? -1 : log2_of(np, 1, 8) + 1;
+    if (a < 0 || b < 0 || c < 0 || d < 0 || e < 0 || split < 0 || split > 2 || mode < 0 || mode > 5) return -1;
+    return ((((((((a * 4 + b) * 3 + c) * 3 + d) * 5 + e) * 3 + split) * 2 + bf16) * 2 + trace) * 6 + mode) * 2 + general;
+  }
+  KernelIndex() {
+    for (int i = 0; i < kKeys; ++i) at[i] = -1;
+    for (int t = 0; t < kNumTables; ++t)
+      for (int i = 0; i < kAllTables[t].count && count < 1024; ++i) {
+        const wsg::KernelEntry& e = kAllTables[t].entries[i];
+        const int k = key(e.tm, e.tn, e.tk, e.nc, e.np, e.split, e.bf16, e.trace, e.mode, e.general);
+        if (k < 0) continue;
+        slots[count] = Slot{&e, 0, 0};
+        at[k] = (int16_t)count++;
+      }
+    for (int i = 0; i < kNumResources; ++i) {
+      const wsg::KernelResources& r = kResources[i];
+      const int k = key(r.tm, r.tn, r.tk, r.nc, r.np, r.split, r.bf16, r.trace, r.mode, r.general);
+      if (k < 0 || at[k] < 0) continue;
+      slots[at[k]].vgprs = r.vgprs;
+      slots[at[k]].agprs = r.agprs;
     }
   }
+};
+
+const KernelIndex::Slot* find_slot(const ws_gemm_config& c, int trace, int mode, int general) {
+  static const KernelIndex index;
+  const int k = KernelIndex::key(c.tile_m, c.tile_n, c.tile_k, c.consumer_waves, c.producer_waves, split_of(c),
+                                 c.dtype == WS_BF16 ? 1 : 0, trace, mode, general);
+  return k < 0 || index.at[k] < 0 ? nullptr : &index.slots[index.at[k]];
+}
+
+const wsg::KernelEntry* find_kernel(const ws_gemm_config& c, int trace = 0, int mode = wsg::kModeGemm,
+                                   int general = 0) {
+  const KernelIndex::Slot* s = find_slot(c, trace, mode, general);
+  return s ? s->kernel : nullptr;
+}
+
+// Registers per wave of the GEMM kernel of c or of its general twin (0, 0 if
+// not in the table).
+void kernel_regs(const ws_gemm_config& c, int general, int* vgprs, int* agprs) {
+  const KernelIndex::Slot* s = find_slot(c, 0, wsg::kModeGemm, general);
+  *vgprs = s ? s->vgprs : 0;
+  *agprs = s ? s->agprs : 0;
 }
 
 wsg::PlanIn plan_in(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int32_t cus,
-                    int32_t occ) {
+                    int32_t occ, int general = 0) {
   wsg::PlanIn in{};
   in.M = M;
   in.N = N;
@@ -110,8 +145,35 @@ wsg::PlanIn plan_in(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, in
   in.split = c.split;
   in.num_cus = cus;
   in.wgs_per_cu = occ;
-  kernel_regs(c, &in.vgprs, &in.agprs);
+  kernel_regs(c, general, &in.vgprs, &in.agprs);
   return in;
+}
+
+// Lets `fn` use a CU's whole LDS on the current device.  Remembered per
+// kernel and device (the setting belongs to the loaded kernel and is never
+// lowered), so that a run does not pay for it again.
+ws_status allow_lds(const void* fn) {
+  int dev = 0;
+  WSG_HIP(hipGetDevice(&dev));
+  constexpr int kSlots = 2048;  // open addressing by the kernel's address; 420 kernels
+  struct Known {
+    std::atomic<const void*> fn;
+    std::atomic<uint64_t> devices;
+  };
+  static Known known[kSlots];
+  Known* k = nullptr;
+  if (dev >= 0 && dev < 64) {
+    size_t h = ((uintptr_t)fn >> 4) % kSlots;
+    for (int i = 0; i < kSlots && !k; ++i, h = (h + 1) % kSlots) {
+      const void* at = known[h].fn.load(std::memory_order_acquire);
+      if (!at && known[h].fn.compare_exchange_strong(at, fn, std::memory_order_acq_rel)) at = fn;
+      if (at == fn) k = &known[h];
+    }
+    if (k && (k->devices.load(std::memory_order_acquire) >> dev & 1)) return WS_OK;
+  }
+  WSG_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, wsg::kLdsLimit));
+  if (k) k->devices.fetch_or(1ull << dev, std::memory_order_acq_rel);
+  return WS_OK;
 }
 
 // A kernel and the grid it is launched with; corner_m >= 0: of the plan's tiles
@@ -161,9 +223,9 @@ void each_part(const ws_gemm_config& c, int cus, int mode, int general, int64_t 
 }
 
 // Workgroups of k's kernel that a CU runs when there are `tiles` of them.
-int per_cu(const ws_gemm_config& k, int64_t tiles, int cus) {
+int per_cu(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
   int v = 0, a = 0;
-  kernel_regs(k, &v, &a);
+  kernel_regs(k, general, &v, &a);
   const int waves = k.consumer_waves + k.producer_waves;
   const int64_t fit = 4 * wsg::waves_per_simd_by_regs(v, a) / waves, want = (tiles + cus - 1) / cus;
   return (int)(want < fit ? want : fit);
@@ -173,8 +235,8 @@ int per_cu(const ws_gemm_config& k, int64_t tiles, int cus) {
 bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm_config k, int64_t tiles, int cus,
                int mode, int general, Launch* l) {
   k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n), 2ll * c.tile_k * (k.tile_m + k.tile_n),
-                              per_cu(k, tiles, cus));
-  if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0), &l->plan) != wsg::kPlanOk) return false;
+                              per_cu(k, general, tiles, cus));
+  if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0, general), &l->plan) != wsg::kPlanOk) return false;
   l->fn = find_kernel(k, 0, mode, general)->fn;
   l->stages = k.stages;
   l->corner_m = l->corner_n = -1;
@@ -251,9 +313,10 @@ ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, i
   } else {
     return WS_OK;
   }
-  for (int i = 0; i < run.count; ++i)
-    WSG_HIP(hipFuncSetAttribute(run.launch[i].fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                run.launch[i].plan.lds_bytes));
+  for (int i = 0; i < run.count; ++i) {
+    const ws_status st = allow_lds(run.launch[i].fn);
+    if (st != WS_OK) return st;
+  }
   *out = run;
   return WS_OK;
 }
@@ -463,18 +526,19 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   WSG_HIP(hipSetDevice(dev));
   int cus = 0;
   WSG_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  WSG_HIP(hipFuncSetAttribute(k->fn, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes));
+  ws_status sl = allow_lds(k->fn);
+  if (sl != WS_OK) return sl;
   int occ = 0;
   WSG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k->fn, p.block, p.lds_bytes));
   if (occ < 1) return WS_ERR_UNSUPPORTED;
   s = wsg::plan_launch(plan_in(M, N, K, *cfg, cus, occ), &p);
   if (s != wsg::kPlanOk) return from_plan(s);
   if (launch_fn != k->fn)
-    WSG_HIP(hipFuncSetAttribute(launch_fn, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes));
+    if ((sl = allow_lds(launch_fn)) != WS_OK) return sl;
   // The general twin may allocate more registers: its own launch.
   wsg::PlanOut pg = p;
   if (general && general != k) {
-    WSG_HIP(hipFuncSetAttribute(general->fn, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes));
+    if ((sl = allow_lds(general->fn)) != WS_OK) return sl;
     int occ_g = 0;
     WSG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ_g, general->fn, p.block, p.lds_bytes));
     if (occ_g < 1) general = nullptr;
@@ -494,6 +558,9 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
     if (ls != WS_OK) return ls;
   }
 
+  const wsg::KernelEntry* traced = (kind == WS_CALIB_NONE && !p.ragged) ? find_kernel(*cfg, 1) : nullptr;
+  if (traced && (sl = allow_lds(traced->fn)) != WS_OK) return sl;
+
   ws_gemm_handle* h = new (std::nothrow) ws_gemm_handle();
   if (!h) return WS_ERR_INVALID_ARG;
   h->M = M;
@@ -510,10 +577,7 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   h->use_general = false;
   h->epi = ws_gemm_epilogue{1.0f, 0.0f, WS_OUT_F32};
   h->calibration = kind != WS_CALIB_NONE;
-  h->traced = (kind == WS_CALIB_NONE && !p.ragged) ? find_kernel(*cfg, 1) : nullptr;
-  if (h->traced)
-    WSG_HIP(hipFuncSetAttribute(h->traced->fn, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                p.lds_bytes));
+  h->traced = traced;
   h->device = dev;
   h->dbg = ws_gemm_debug{0, 0, 0};
   h->trace = nullptr;
@@ -741,11 +805,10 @@ ws_status ws_gemm_run_noalloc(int64_t M, int64_t N, int64_t K, const ws_gemm_con
   StaticDevice sd;
   const ws_status st = static_device(dev, &sd);
   if (st != WS_OK) return st;
-  WSG_HIP(hipFuncSetAttribute(k->fn, hipFuncAttributeMaxDynamicSharedMemorySize, p.lds_bytes));
-  int occ = 0;
-  WSG_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k->fn, p.block, p.lds_bytes));
-  if (occ < 1) return WS_ERR_UNSUPPORTED;
-  s = wsg::plan_launch(plan_in(M, N, K, *cfg, sd.cus, occ), &p);
+  const ws_status sl = allow_lds(k->fn);
+  if (sl != WS_OK) return sl;
+  // resident workgroups from the compiled kernel's registers: what the runtime's occupancy query gives
+  s = wsg::plan_launch(plan_in(M, N, K, *cfg, sd.cus, 0, p.ragged), &p);
   if (s != wsg::kPlanOk) return from_plan(s);
   Run run{{{k->fn, p, cfg->stages, -1, -1}, {}}, 1};
   const ws_status ls = choose_run(M, N, K, *cfg, sd.cus, wsg::kModeGemm, p.ragged, true, &run);
