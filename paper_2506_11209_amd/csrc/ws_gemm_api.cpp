@@ -200,7 +200,7 @@ ws_gemm_config part_of(const ws_gemm_config& c, int tm, int tn) {
   ws_gemm_config k = c;
   k.tile_m = tm;
   k.tile_n = tn;
-  k.split = split_of(c);
+  if (c.producer_waves > 0) k.split = split_of(c);  // 0 for the synchronous kernel
   if (c.consumer_waves == 8 && (tm < c.tile_m || tn < c.tile_n)) k.consumer_waves = 4;
   return k;
 }
@@ -234,8 +234,9 @@ int per_cu(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
 // Plan of `tiles` tiles of part k of c on the M x N x K problem.
 bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm_config k, int64_t tiles, int cus,
                int mode, int general, Launch* l) {
-  k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n), 2ll * c.tile_k * (k.tile_m + k.tile_n),
-                              per_cu(k, general, tiles, cus));
+  if (c.producer_waves > 0)  // the synchronous kernel's depth says whether it overlaps: kept
+    k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n),
+                                2ll * c.tile_k * (k.tile_m + k.tile_n), per_cu(k, general, tiles, cus));
   if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0, general), &l->plan) != wsg::kPlanOk) return false;
   l->fn = find_kernel(k, 0, mode, general)->fn;
   l->stages = k.stages;
@@ -248,15 +249,14 @@ bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm
 // tiles and, in a second launch, the rest in parts - the rest being partial
 // edge tiles, which would multiply padding for a round of their own, or what a
 // nearly empty last round would take.  plain_block: the block's tiles may run
-// the plain kernel (default epilogue; they are whole).  Specialised kernels
-// only: the synchronous one is the baseline at its tile.
+// the plain kernel (default epilogue; they are whole).  The synchronous kernel
+// walks one tile region: whole tiles or parts.
 //
 // Measured, whole tiles -> block and rest: 4100x4104x4104 with 256x256x64 tiles
 // (289 tiles, 33 of them almost all padding) 199 -> 148 us, as 128x128 parts
 // 269 us.
 ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int mode, int general,
                      bool plain_block, Run* out) {
-  if (c.producer_waves == 0) return WS_OK;
   const Launch& whole = out->launch[0];
   // costs of the whole problem: part_cost units are ns per 64 of K
   const int64_t slabs = (K + 63) / 64;
@@ -269,7 +269,7 @@ ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, i
               best = cost * slabs;
             });
   int rows_best = 0, cols_best = 0;
-  if (mode == wsg::kModeGemm) {
+  if (mode == wsg::kModeGemm && c.producer_waves > 0) {
     const int64_t rows = M / c.tile_m, cols = N / c.tile_n, rounds = rows * cols / cus;
     for (int t = 0; t < 3 && rows > 0 && cols > 0; ++t) {
       // all whole tiles, or as many rows (columns) of them as whole rounds hold

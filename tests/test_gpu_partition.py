@@ -91,6 +91,24 @@ def test_partitioned_products_are_exact(shape, launch, dtype, path):
         g.close()
 
 
+@pytest.mark.parametrize("shape,tile,P,nc", [((768, 512, 192), (256, 128, 64), 1, 4),
+                                             ((512, 512, 128), (256, 256, 64), 1, 4),
+                                             ((384, 1024, 96), (128, 128, 32), 2, 4),
+                                             ((256, 192, 64), (64, 64, 32), 2, 1)], ids=str)
+def test_synchronous_parts_are_exact(shape, tile, P, nc):
+    M, N, K = shape
+    log("case synchronous parts %s %s" % (shape, tile))
+    A, B = inputs.make_operands(M, N, K, "bf16", "int4", M + K)
+    g = w.WsGemm(M, N, K, tile, P, 0, nc, "bf16")
+    try:
+        C = torch.full((M, N), float("nan"), device="cuda")
+        g(A.cuda(), B.cuda(), C)
+        assert g.sync_status() == w.WS_OK
+        check(C.cpu().numpy(), A, B, "bf16", tile[0])
+    finally:
+        g.close()
+
+
 def test_two_launch_run_under_capture_and_the_launch_clock():
     M, N, K = 2056, 2056, 1304
     log("case partition capture")
