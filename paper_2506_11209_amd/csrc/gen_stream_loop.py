@@ -36,6 +36,17 @@ then run along the wave tile's longer side, so that each fragment's last use
 in k-step t and its first use in k-step t + 1 are four MFMAs apart, and each
 fragment is read again right behind its last use.
 
+At KS = 4, F = 4 the check of K-iteration u + 1 stands in u's second k-step,
+two before u's slot is released.  Where the slot is not full (after a second
+look) and the ring has two or three slots, the block drains instead of waiting
+there: it releases u's slot, whose reads have all completed, multiplies the rest
+of u and then waits, so that a ring of three slots is not one of two while the
+consumers wait.  It then reads u + 1 with nothing to multiply, which deeper
+rings do not win back.  Waiting -> draining, 64x64x64: two slots
+1024x1024x8192 75 -> 51 us, three slots 4096^3 261 -> 252 us (LDS-DMA 269 ->
+241), 64x4096x4096 23.3 -> 21.3 us; 128x128x64 2048x2048x32768 three slots
+286 -> 279 us, four slots 264 -> 265 us and the general kernel 277 -> 302 us.
+
 The loop body is U = lcm(KS, F) k-steps, m = U / KS K-iterations.  A tile
 whose S is not a multiple of m enters its first body at the k-step that makes
 the rest whole (one prologue per remainder).  Tiles with S < m take the
@@ -96,6 +107,7 @@ class Cfg:
         self.ahead = max(1, self.f - 1)               # k-steps read ahead
         self.body = self.ks * self.f // math.gcd(self.ks, self.f)
         self.m = self.body // self.ks                 # K-iterations per loop body
+        self.drain = self.f == 4 and self.ks == 4     # see the module's text
         assert self.ahead <= self.ks + 1 and self.ahead < self.body
         assert self.bm * self.bn * 16 + self.f * self.set_regs <= self.vgprs - 16
         assert self.f > 1 or sorted((self.bm, self.bn)) == [2, 4]
@@ -113,14 +125,17 @@ def spread(mfmas, filler):
     return out
 
 
-def program(E: Emitter, c: Cfg, bf16: bool, S: int | None):
+def program(E: Emitter, c: Cfg, bf16: bool, S: int | None, drains=()):
     """Emit the block.  With S given (a dry run) only the path of a tile of S
-    K-iterations is emitted, with absolute k-step numbers in the tags; with
-    S None every segment is emitted once."""
+    K-iterations is emitted, with absolute k-step numbers in the tags, draining
+    in the loop bodies listed in `drains`; with S None every segment is emitted
+    once."""
     mfma = "v_mfma_f32_32x32x16_bf16" if bf16 else "v_mfma_f32_32x32x16_f16"
     KS, F, U, m, D = c.ks, c.f, c.body, c.m, c.ahead
     emit = E.emit
     stubs = []                     # (label, kind) of out-of-line code
+    drained = []                   # (k-step, MFMAs left of it) where a drain leaves the body
+    dry = S is not None
     label = [20]
 
     def new_label():
@@ -189,7 +204,7 @@ def program(E: Emitter, c: Cfg, bf16: bool, S: int | None):
     def enter(site, u):
         # the read stream moves on to K-iteration u > 0
         k = new_label()
-        stubs.append((k, "poll"))
+        stubs.append((k, "drain" if c.drain and site[0] == "body" else "poll"))
         stubs.append((k + 1000, "delay"))
         return [[("wait", site, ("peek", u))] + ins("v_readfirstlane_b32 %[t0], %[vp]"),
                 ins("s_sub_u32 %[t0], %[t0], %[rt]", "s_cmp_lt_i32 %[t0], 0", "s_cbranch_scc1 %df" % k,
@@ -262,8 +277,67 @@ def program(E: Emitter, c: Cfg, bf16: bool, S: int | None):
             if (t + D) % KS == 0:
                 filler += enter((seg, j, "enter"), (t + D) // KS)
             filler += reads(t + D)
-        for unit in spread(mfmas(t), filler):
+        units = spread(mfmas(t), filler)
+        if c.drain and seg == "body" and (t + D) % KS == 0:
+            at = next(i for i, unit in enumerate(units) if any("s_cbranch" in x[1] for x in unit))
+            rest = [unit for unit in units[at + 1:] if "v_mfma" in unit[0][1]]
+            if dry and t // U in drains:
+                for unit in units[:at + 1]:
+                    put(unit)
+                drain(t, rest)
+                return True
+            drained.append((t, rest))
+        for unit in units:
             put(unit)
+        return False
+
+    def drain(t, rest):
+        # The slot of the K-iteration to enter, u, is not full.  Every read so
+        # far has completed: release the slot of u - 1, multiply its k-steps
+        # t (what is left of it) .. t + D - 1, and only then wait for u and
+        # read its first D k-steps, which is the state at the body's start.
+        u = (t + D) // KS
+        E.ops.clear()
+        for unit in release(u - 1):
+            put(unit)
+        for unit in rest + [m for x in range(t + 1, t + D) for m in mfmas(x)]:
+            put(unit)
+        if not dry:
+            poll(2900, 2901)
+        put(next_slot())
+        put(ins("v_add_u32 %[vb], %[rb], %[boff]"))
+        for unit in peek(u + 1):
+            put(unit)
+        for x in range(t + D, t + 2 * D):
+            for unit in reads(x):
+                put(unit)
+
+    def poll(again, full):
+        # poll K-iteration u's counter (address fa, target rt) until it is full
+        emit("s_mov_b32 %[spins], 0")
+        emit("%d:" % again)
+        emit("v_mov_b32 %[vx], %[fa]")
+        emit("ds_read_b32 %[vp], %[vx]")
+        emit("v_mov_b32 %[vx], %[abortb]")
+        emit("ds_read_b32 %[vx], %[vx]")
+        emit("s_waitcnt lgkmcnt(0)")
+        emit("v_readfirstlane_b32 %[t0], %[vp]")
+        emit("s_sub_u32 %[t0], %[t0], %[rt]")
+        emit("s_cmp_ge_i32 %[t0], 0")
+        emit("s_cbranch_scc1 %d%s" % (full, "f" if full == again + 1 else "b"))
+        emit("v_readfirstlane_b32 %[t0], %[vx]")
+        emit("s_mov_b32 %[st], 1")
+        emit("s_cmp_lg_u32 %[t0], 0")
+        emit("s_cbranch_scc1 9b")
+        emit("s_add_u32 %[spins], %[spins], 1")
+        emit("s_mov_b32 %[st], 2")
+        emit("s_cmp_gt_i32 %[spins], %[lim]")
+        emit("s_cbranch_scc1 9b")
+        emit("s_mov_b32 %[st], 0")
+        emit("s_sleep 1")
+        emit("s_branch %db" % again)
+        if full == again + 1:
+            emit("%d:" % full)
 
     def prologue(j0):
         # reads of the tile's first D k-steps, which sit at body position j0 ..
@@ -282,7 +356,6 @@ def program(E: Emitter, c: Cfg, bf16: bool, S: int | None):
     emit("v_mov_b32 %[one], 1")
     emit("v_add_u32 %[vb], %[rb], %[boff]")
     rems = [0] if S is None else [S % m]
-    dry = S is not None
     j0s = {r: ((m - r) % m) * KS for r in range(m)}
 
     def kk(extra):
@@ -311,6 +384,7 @@ def program(E: Emitter, c: Cfg, bf16: bool, S: int | None):
             if m == 2 and j == KS:
                 emit("11:")
             kstep("body", j, j, True)
+        emit("13:")
         emit("s_sub_u32 %[kk], %[kk], 1")
         emit("s_cmp_lg_u32 %[kk], 0")
         emit("s_cbranch_scc1 1b")
@@ -325,8 +399,8 @@ def program(E: Emitter, c: Cfg, bf16: bool, S: int | None):
         for b in range(n):
             for j in range(U):
                 t = b * U + j
-                if t >= j0:
-                    kstep("tail" if b == n - 1 else "body", j, t, b < n - 1 or j + D < U)
+                if t >= j0 and kstep("tail" if b == n - 1 else "body", j, t, b < n - 1 or j + D < U):
+                    break
     # the next tile's first slot; its counter and target are in fa and rt
     for l in next_slot():
         emit(l[1])
@@ -358,29 +432,25 @@ def program(E: Emitter, c: Cfg, bf16: bool, S: int | None):
             emit("s_cbranch_scc1 %db" % (k + 2000))
             emit("s_branch %db" % (k + 1))
             continue
-        # poll K-iteration u's counter (address fa, target rt) until it is full
-        emit("s_mov_b32 %[spins], 0")
-        emit("%d:" % (k + 2000))
-        emit("v_mov_b32 %[vx], %[fa]")
-        emit("ds_read_b32 %[vp], %[vx]")
-        emit("v_mov_b32 %[vx], %[abortb]")
-        emit("ds_read_b32 %[vx], %[vx]")
-        emit("s_waitcnt lgkmcnt(0)")
-        emit("v_readfirstlane_b32 %[t0], %[vp]")
-        emit("s_sub_u32 %[t0], %[t0], %[rt]")
-        emit("s_cmp_ge_i32 %[t0], 0")
-        emit("s_cbranch_scc1 %db" % (k + 1))
-        emit("v_readfirstlane_b32 %[t0], %[vx]")
-        emit("s_mov_b32 %[st], 1")
-        emit("s_cmp_lg_u32 %[t0], 0")
-        emit("s_cbranch_scc1 9b")
-        emit("s_add_u32 %[spins], %[spins], 1")
-        emit("s_mov_b32 %[st], 2")
-        emit("s_cmp_gt_i32 %[spins], %[lim]")
-        emit("s_cbranch_scc1 9b")
-        emit("s_mov_b32 %[st], 0")
-        emit("s_sleep 1")
-        emit("s_branch %db" % (k + 2000))
+        if kind == "drain":
+            # one more look, then drain if the ring has at most three slots
+            emit("v_mov_b32 %[vx], %[fa]")
+            emit("ds_read_b32 %[vp], %[vx]")
+            emit("s_waitcnt lgkmcnt(0)")
+            emit("v_readfirstlane_b32 %[t0], %[vp]")
+            emit("s_sub_u32 %[t0], %[t0], %[rt]")
+            emit("s_cmp_ge_i32 %[t0], 0")
+            emit("s_cbranch_scc1 %db" % (k + 1))
+            emit("s_sub_u32 %[t0], %[rend], %[ring]")
+            emit("s_cmp_gt_u32 %%[t0], %d" % (3 * c.stage))
+            emit("s_cbranch_scc1 2990f")
+            (t, rest), = drained  # one such site per block
+            drain(t, rest)
+            emit("s_branch 13b")
+            emit("2990:")
+            poll(2950, k + 1)
+            continue
+        poll(k + 2000, k + 1)
     emit("19:")
 
 
@@ -393,10 +463,11 @@ def tile_iters(c: Cfg):
 def gen_block(c: Cfg, bf16: bool) -> list[str]:
     waits = {}
     for S in tile_iters(c):
-        E = Emitter()
-        program(E, c, bf16, S)
-        for site, n in E.need.items():
-            waits[site] = min(waits.get(site, LGKM_MAX), n)
+        for drains in ((), range(0, 9, 2), range(1, 9, 2), range(9)) if c.drain else ((),):
+            E = Emitter()
+            program(E, c, bf16, S, drains)
+            for site, n in E.need.items():
+                waits[site] = min(waits.get(site, LGKM_MAX), n)
     E = Emitter(waits)
     program(E, c, bf16, None)
     return E.lines

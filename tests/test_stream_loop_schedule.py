@@ -246,7 +246,7 @@ class Sim:
             elif op.startswith("s_cmp"):
                 a, b = self.val(args[0]), self.val(args[1])
                 scc = {"s_cmp_eq_u32": a == b, "s_cmp_lg_u32": a != b, "s_cmp_lt_i32": a < b,
-                       "s_cmp_ge_i32": a >= b, "s_cmp_gt_i32": a > b}[op]
+                       "s_cmp_ge_i32": a >= b, "s_cmp_gt_i32": a > b, "s_cmp_gt_u32": a > b}[op]
             else:
                 raise AssertionError("the checker does not know %r" % l)
 
