@@ -7,7 +7,8 @@
  * with the tiling tuple (T_M, T_N, T_K) of the same section: A is cut into
  * T_M x T_K tiles, B into T_K x T_N tiles, C into T_M x T_N tiles.
  *
- * Each output tile is computed by one workgroup in which producer (DMA)
+ * Each output tile is computed by one workgroup (or in parts by several, see
+ * "Tile parts") in which producer (DMA)
  * wavefronts stream the A and B tiles of every K-iteration into a circular
  * buffer in LDS and consumer (MATH) wavefronts pop them, multiply-accumulate
  * and store the tile (Background, "The Warp Specialized GeMM Kernel in
@@ -30,8 +31,10 @@
  * arrangement (four consumer waves for parts of a 256 x 256 tile), with the
  * ring's bytes shared out over more, smaller K-iterations.  Results are the
  * same to the bit (every element takes its products in the same order), and
- * the plan a handle reports stays that of its whole tiles; calibration
- * kernels take the parts of the GEMM they calibrate, traced runs whole tiles.
+ * the plan a handle reports stays that of its whole tiles.  A block of whole
+ * tiles may also run first and the rest, in parts, as a second launch of the
+ * same run.  Calibration kernels (except the empty one) take parts likewise,
+ * always in one launch; traced runs take whole tiles.
  *
  * Data layout: A, B and C are dense and row-major (leading dimensions K, N
  * and N).  A and B hold IEEE binary16 (WS_F16) or bfloat16 (WS_BF16)
@@ -189,7 +192,7 @@ ws_status ws_gemm_sync_status(ws_gemm_t h, hipStream_t stream);
 
 /* Average shader clock of the runs since the last call (a measurement hook
  * for reporting a launch's fraction of peak against the clock it ran at).
- * Every GEMM launch of the handle has workgroup 0's first wave read the
+ * Every run of the handle (its main launch) has workgroup 0's first wave read the
  * shader-clock counter (s_memtime) and the 100 MHz reference counter
  * (s_memrealtime) at its start and its end and add the differences to two
  * device accumulators.  This call synchronises `stream`, returns the sums
