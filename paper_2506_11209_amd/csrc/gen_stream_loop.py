@@ -298,6 +298,7 @@ def program(E: Emitter, c: Cfg, bf16: bool, S: int | None, drains=()):
         # read its first D k-steps, which is the state at the body's start.
         u = (t + D) // KS
         E.ops.clear()
+        emit("s_waitcnt lgkmcnt(0)")  # the second look's wait, again on the release's own straight line
         for unit in release(u - 1):
             put(unit)
         for unit in rest + [m for x in range(t + 1, t + D) for m in mfmas(x)]:
