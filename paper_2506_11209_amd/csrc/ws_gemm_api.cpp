@@ -207,6 +207,9 @@ ws_gemm_config part_of(const ws_gemm_config& c, int tm, int tn) {
 
 // Calls f(config, cost) for every compiled part of c's tile (the whole tile
 // left out) that is cheaper than `limit`: `count(config)` tiles of it.
+// 32 x 32 parts have one consumer wave and are for tiles of one consumer wave
+// only: its one loading wave takes 390 ns for 64 of K, four loading waves 280 ns
+// for a 64 x 64 tile (48x4096x4096: 256 such parts 28.9 us, 64 tiles 22.9 us).
 template <typename Count, typename F>
 void each_part(const ws_gemm_config& c, int cus, int mode, int general, int64_t limit, Count count, F f) {
   const int least = c.consumer_waves == 1 ? 32 : 64;
