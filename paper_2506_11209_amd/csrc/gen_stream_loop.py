@@ -475,8 +475,12 @@ def gen_block(c: Cfg, bf16: bool) -> list[str]:
 
 
 def gen_struct(c: Cfg, bf16: bool) -> str:
+    # Every in/out operand is early-clobber: the block writes it long before it
+    # last reads its inputs, and the cursor starts out equal to some of them
+    # (slot and ring, full and full0, empty and empty0), which would else let
+    # the compiler give both one register.
     lines = gen_block(c, bf16)
-    acc_ops = ", ".join('[c%d_%d] "+v"(c[%d][%d])' % (mb, nb, mb, nb) for mb in range(c.bm) for nb in range(c.bn))
+    acc_ops = ", ".join('[c%d_%d] "+&v"(c[%d][%d])' % (mb, nb, mb, nb) for mb in range(c.bm) for nb in range(c.bn))
     ao = ", ".join('[ao%d] "v"(a_off[%d])' % (k, k) for k in range(c.ks if c.f > 1 else 1))
     clobbers = ", ".join('"v%d"' % r for r in range(c.frag_base, c.vgprs))
     body = "\n".join('        "%s\\n\\t"' % l for l in lines)
@@ -492,7 +496,7 @@ struct StreamLoop<%(tm)d, %(tn)d, %(tk)d, %(nc)d, %(np)d, %(bf16)s> {
     uint32_t st, kk, t0, spins, va, vb, vp, vx, one;
     asm volatile(
 %(body)s
-        : %(acc)s, [rb] "+s"(r.slot), [fa] "+s"(r.full), [rt] "+s"(r.target), [ea] "+s"(r.empty),
+        : %(acc)s, [rb] "+&s"(r.slot), [fa] "+&s"(r.full), [rt] "+&s"(r.target), [ea] "+&s"(r.empty),
           [st] "=&s"(st), [kk] "=&s"(kk), [t0] "=&s"(t0), [spins] "=&s"(spins), [va] "=&v"(va),
           [vb] "=&v"(vb), [vp] "=&v"(vp), [vx] "=&v"(vx), [one] "=&v"(one)
         : %(ao)s, [boff] "v"(boff), [S] "s"(S), [ring] "s"(r.ring), [rend] "s"(r.ring_end),

@@ -280,6 +280,31 @@ def test_committed_file_is_what_the_generator_writes():
     assert set(BLOCKS) == {k + (b,) for k in gen.CONFIGS for b in (True, False)}
 
 
+def shared_register_hazards(text):
+    """In/out operands of the asm statements in `text` that are written while an
+    input is still to be read, without being marked early-clobber: the compiler
+    may give such an operand and an input of equal value one register."""
+    out = []
+    for body, outs, ins in re.findall(r'asm volatile\(\n(.*?)\n\s+: (.*?)\n\s+: (.*?)\n\s+: "memory"', text, re.S):
+        lines = [l.strip() for l in re.findall(r'^\s*"(.*)\\n\\t"$', body, re.M)]
+        inputs = re.findall(r'\[(\w+)\] "(?:s|v)"', ins)
+        last = max(i for i, l in enumerate(lines) if any("%%[%s]" % n in l for n in inputs))
+        for name, mark in re.findall(r'\[(\w+)\] "\+(&?)[sv]"', outs):
+            wr = [i for i, l in enumerate(lines) if re.match(r"(?:v_|s_(?!cmp|cbranch))\S+ %%\[%s\]," % name, l)]
+            assert wr, name
+            if not mark and wr[0] < last:
+                out.append(name)
+    return out
+
+
+def test_operands_written_early_share_no_register_with_an_input():
+    with open(gen.OUT) as f:
+        text = f.read()
+    assert text.count("asm volatile(") == len(BLOCKS)
+    assert not shared_register_hazards(text)
+    assert set(shared_register_hazards(text.replace('"+&s"', '"+s"'))) == {"rb", "fa", "rt", "ea"}
+
+
 @pytest.mark.parametrize("key", sorted(k for k in BLOCKS if k[5]), ids=str)
 def test_planted_mistakes_are_caught(key):
     lines, c = BLOCKS[key], gen.Cfg(*key[:5])
