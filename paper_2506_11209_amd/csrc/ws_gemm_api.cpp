@@ -328,23 +328,20 @@ ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, i
 ws_status launch_run(const Run& run, wsg::KernelArgs a, hipStream_t stream) {
   for (int i = 0; i < run.count; ++i) {
     const Launch& l = run.launch[i];
-    a.tiles_m = l.plan.tiles_m;
-    a.tiles_n = l.plan.tiles_n;
-    a.num_tiles = l.plan.tiles;
+    const wsg::TileRegions r =
+        wsg::tile_regions(l.plan.tiles_m, l.plan.tiles_n, l.plan.group_m, l.corner_m, l.corner_n);
+    a.tiles_m = r.tiles_m;
+    a.tiles_n = r.tiles_n;
+    a.group_m = r.group_m;
+    a.region2 = r.region2;
+    a.row1 = r.row1;
+    a.tiles2_m = r.tiles2_m;
+    a.tiles2_n = r.tiles2_n;
+    a.col2 = r.col2;
+    a.num_tiles = r.num_tiles;
     a.iters = l.plan.iters;
     a.stages = l.stages;
-    a.group_m = l.plan.group_m;
     a.xcd_remap = l.plan.xcd_remap;
-    a.region2 = INT32_MAX;
-    a.row1 = a.tiles2_m = a.tiles2_n = a.col2 = 0;
-    if (l.corner_m >= 0) {  // the rows below the block, then the columns right of it, down the rows first
-      a.row1 = l.corner_m;
-      a.tiles_m = a.group_m = l.plan.tiles_m - l.corner_m;
-      a.region2 = a.tiles_m * l.plan.tiles_n;
-      a.tiles2_m = l.corner_m;
-      a.tiles2_n = l.plan.tiles_n - l.corner_n;
-      a.col2 = l.corner_n;
-    }
     if (i > 0) a.clock = nullptr;  // one clock sample per run, of its main launch
     void* params[] = {&a};
     WSG_HIP(hipLaunchKernel(l.fn, dim3(l.plan.grid), dim3(l.plan.block), params, (size_t)l.plan.lds_bytes, stream));

@@ -113,10 +113,7 @@ struct KernelArgs {
   // cycles and the 100 MHz reference ticks it spans to clock[0] and clock[1],
   // and 1 to clock[2]; their ratio is the average shader clock of the launch.
   unsigned long long* clock;
-  // Second tile region: schedule indices from region2 on walk tiles2_m x
-  // tiles2_n tiles whose first column is col2; the ones before walk the first
-  // region (tiles_m, tiles_n, group_m), whose first row is row1.  One region:
-  // region2 is past every index and row1 is 0.
+  // Second tile region (see TileRegions).
   int32_t region2, row1, tiles2_m, tiles2_n, col2;
 };
 
@@ -707,11 +704,9 @@ __device__ __forceinline__ void store_tile(const KernelArgs& args, const f32x16_
 // Per-workgroup tile sequence (identical in both roles).
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void tile_at(const KernelArgs& args, int v, int* ti, int* tj) {
-  const bool second = v >= args.region2;
-  tile_coords(second ? v - args.region2 : v, second ? args.tiles2_m : args.tiles_m,
-              second ? args.tiles2_n : args.tiles_n, second ? args.tiles2_m : args.group_m, ti, tj);
-  *ti += second ? 0 : args.row1;
-  *tj += second ? args.col2 : 0;
+  const TileRegions r{args.tiles_m, args.tiles_n, args.group_m, args.region2, args.row1, args.tiles2_m, args.tiles2_n,
+                      args.col2, args.num_tiles};
+  region_tile(r, v, ti, tj);
 }
 __device__ __forceinline__ int first_slot(const KernelArgs& args) {
   const int G = gridDim.x;

@@ -34,6 +34,38 @@ WSG_HD inline void tile_coords(int v, int tiles_m, int tiles_n, int group_m, int
   *tj = rem / rows;
 }
 
+// The tiles of one launch.  Schedule indices from region2 on walk tiles2_m x
+// tiles2_n tiles whose first column is col2; the ones before walk the first
+// region (tiles_m, tiles_n, group_m), whose first row is row1.  One region:
+// region2 is past every index and row1 is 0.
+struct TileRegions {
+  int32_t tiles_m, tiles_n, group_m, region2, row1, tiles2_m, tiles2_n, col2, num_tiles;
+};
+
+// Tile (ti, tj) of schedule index v.  The consumers step to the index one grid
+// past their last tile and drop the answer; there the raster would divide by the
+// rows (columns) of a group that holds none, so past the end it is the last tile.
+WSG_HD inline void region_tile(const TileRegions& r, int v, int* ti, int* tj) {
+  v = v < r.num_tiles ? v : r.num_tiles - 1;
+  const bool second = v >= r.region2;
+  tile_coords(second ? v - r.region2 : v, second ? r.tiles2_m : r.tiles_m, second ? r.tiles2_n : r.tiles_n,
+              second ? r.tiles2_m : r.group_m, ti, tj);
+  *ti += second ? 0 : r.row1;
+  *tj += second ? r.col2 : 0;
+}
+
+// Regions of the tiles_m x tiles_n tiles of a plan (raster groups of group_m
+// rows) or, with corner_m >= 0, of those outside the block of the first corner_m
+// rows and corner_n columns: the rows below the block, then the columns right
+// of it, down the rows first.
+inline TileRegions tile_regions(int tiles_m, int tiles_n, int group_m, int corner_m, int corner_n) {
+  const int all = tiles_m * tiles_n;
+  if (corner_m < 0) return TileRegions{tiles_m, tiles_n, group_m, INT32_MAX, 0, 0, 0, 0, all};
+  const int below = tiles_m - corner_m, right = tiles_n - corner_n;
+  return TileRegions{below, tiles_n, below, below * tiles_n, corner_m, corner_m, right, corner_n,
+                     all - corner_m * corner_n};
+}
+
 // Workgroup id -> schedule slot.  Workgroup g runs on XCD g % 8; the remap
 // gives XCD x the consecutive slots [x * G/8, (x+1) * G/8), so tiles that run
 // concurrently on one XCD are neighbours in the raster.  Requires G % 8 == 0.
