@@ -34,7 +34,9 @@
  * the plan a handle reports stays that of its whole tiles.  A block of whole
  * tiles may also run first and the rest, in parts, as a second launch of the
  * same run.  Calibration kernels (except the empty one) take parts likewise,
- * always in one launch; traced runs take whole tiles.
+ * always in one launch; traced runs take whole tiles.  ws_gemm_query_launches
+ * reports what a run launches, ws_gemm_set_partition keeps a handle to the
+ * requested tile and ring.
  *
  * Data layout: A, B and C are dense and row-major (leading dimensions K, N
  * and N).  A and B hold IEEE binary16 (WS_F16) or bfloat16 (WS_BF16)
@@ -145,6 +147,25 @@ typedef struct {
   int32_t consumer_delay; /* extra ~8k-cycle sleeps per K-iteration in every consumer */
 } ws_gemm_debug;
 
+/* How the library cuts the output of later runs of a handle. */
+typedef enum {
+  WS_PARTITION_AUTO = 0, /* "Tile parts" above: the library may compute tiles in parts */
+  WS_PARTITION_WHOLE = 1 /* exactly the configuration's tile, waves and ring: one launch, with the
+                            plan of ws_gemm_query */
+} ws_partition;
+
+/* One kernel launch of a run. */
+#define WS_MAX_LAUNCHES 2
+typedef struct {
+  int32_t tile_m, tile_n, tile_k, stages, producer_waves, consumer_waves, split; /* the kernel's own */
+  int32_t general;                 /* 1: the general kernel variant */
+  int32_t grid, block, lds_bytes;
+  int32_t tiles_m, tiles_n;        /* tiles of this size that cover C (the block, for a first of two) */
+  int32_t tiles, rounds, iters;    /* tiles computed, dispatch rounds, K-iterations per tile */
+  int32_t skip_m, skip_n;          /* of tiles_m x tiles_n, the first skip_m rows of skip_n columns
+                                      are left out: an earlier launch of the run computes them */
+} ws_gemm_launch_info;
+
 /* ABI version of the loaded library (WS_GEMM_ABI_VERSION). */
 int32_t ws_gemm_abi_version(void);
 
@@ -164,6 +185,15 @@ const char* ws_gemm_last_error(void);
  * Fills *out on WS_OK. */
 ws_status ws_gemm_plan(int64_t M, int64_t N, int64_t K, const ws_gemm_config* cfg,
                        int32_t num_cus, int32_t wgs_per_cu, ws_gemm_plan_info* out);
+
+/* The launches of a run on a device of num_cus compute units: out[0] ..
+ * out[*count - 1] (WS_MAX_LAUNCHES at most, 0 for an empty problem), in stream
+ * order.  general: of a handle with another than the default epilogue.
+ * Host-only; what ws_gemm_run_noalloc launches and, where the runtime's
+ * occupancy is the planner's, ws_gemm_run. */
+ws_status ws_gemm_plan_launches(int64_t M, int64_t N, int64_t K, const ws_gemm_config* cfg,
+                                int32_t num_cus, int32_t general, ws_gemm_launch_info* out,
+                                int32_t* count);
 
 /* Output tile (tile_m_idx, tile_n_idx) that workgroup `wg` computes in
  * dispatch round `round` under plan `info` (as filled by ws_gemm_plan or
@@ -205,6 +235,14 @@ ws_status ws_gemm_clock(ws_gemm_t h, hipStream_t stream, uint64_t* shader_cycles
 
 /* The plan a handle launches with (of whole tiles, see "Tile parts" above). */
 ws_status ws_gemm_query(ws_gemm_t h, ws_gemm_plan_info* out);
+
+/* ws_partition of later runs; WS_PARTITION_AUTO at first.  For measuring or
+ * testing one kernel: by default a launch of few tiles runs other kernels than
+ * the configuration's own.  Results are the same to the bit. */
+ws_status ws_gemm_set_partition(ws_gemm_t h, int32_t partition);
+
+/* The launches of the handle's next run, as ws_gemm_plan_launches gives them. */
+ws_status ws_gemm_query_launches(ws_gemm_t h, ws_gemm_launch_info* out, int32_t* count);
 
 /* Epilogue of later runs (NULL restores the default).  A non-default
  * epilogue switches the handle to the general kernel variant, with its own

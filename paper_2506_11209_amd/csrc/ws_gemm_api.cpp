@@ -180,8 +180,9 @@ ws_status allow_lds(const void* fn) {
 // only those outside the block of the first corner_m rows and corner_n columns.
 struct Launch {
   const void* fn;
+  ws_gemm_config cfg;  // of the kernel: its tile, waves and ring
+  int32_t general;
   wsg::PlanOut plan;
-  int32_t stages;
   int32_t corner_m, corner_n;
 };
 // What one run launches, in stream order.
@@ -189,6 +190,12 @@ struct Run {
   Launch launch[2];
   int count;
 };
+static_assert(sizeof(Run::launch) / sizeof(Launch) == WS_MAX_LAUNCHES, "header and library agree");
+
+// One launch of every tile.
+Run whole_run(const void* fn, const ws_gemm_config& c, int general, const wsg::PlanOut& plan) {
+  return Run{{{fn, c, general, plan, -1, -1}, {}}, 1};
+}
 
 int64_t tiles_of(int64_t M, int64_t N, const ws_gemm_config& k) {
   return ((M + k.tile_m - 1) / k.tile_m) * ((N + k.tile_n - 1) / k.tile_n);
@@ -240,10 +247,9 @@ bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm
   if (c.producer_waves > 0)  // the synchronous kernel's depth says whether it overlaps: kept
     k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n),
                                 2ll * c.tile_k * (k.tile_m + k.tile_n), per_cu(k, general, tiles, cus));
-  if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0, general), &l->plan) != wsg::kPlanOk) return false;
-  l->fn = find_kernel(k, 0, mode, general)->fn;
-  l->stages = k.stages;
-  l->corner_m = l->corner_n = -1;
+  wsg::PlanOut plan;
+  if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0, general), &plan) != wsg::kPlanOk) return false;
+  *l = Launch{find_kernel(k, 0, mode, general)->fn, k, general, plan, -1, -1};
   return true;
 }
 
@@ -258,8 +264,8 @@ bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm
 // Measured, whole tiles -> block and rest: 4100x4104x4104 with 256x256x64 tiles
 // (289 tiles, 33 of them almost all padding) 199 -> 148 us, as 128x128 parts
 // 269 us.
-ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int mode, int general,
-                     bool plain_block, Run* out) {
+void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int mode, int general,
+                bool plain_block, Run* out) {
   const Launch& whole = out->launch[0];
   // costs of the whole problem: part_cost units are ns per 64 of K
   const int64_t slabs = (K + 63) / 64;
@@ -299,12 +305,15 @@ ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, i
     Launch& e = run.launch[1];
     if (wsg::plan_launch(plan_in((int64_t)rows_best * c.tile_m, (int64_t)cols_best * c.tile_n, K, c, cus, 0),
                          &m.plan) != wsg::kPlanOk)
-      return WS_OK;
+      return;
     const wsg::KernelEntry* plain = plain_block && K % c.tile_k == 0 ? find_kernel(c, 0, mode, 0) : nullptr;
-    if (plain) m.fn = plain->fn;
+    if (plain) {
+      m.fn = plain->fn;
+      m.general = 0;
+    }
     const int cm = rows_best * (c.tile_m / rest.tile_m), cn = cols_best * (c.tile_n / rest.tile_n);
     const int64_t tiles = tiles_of(M, N, rest) - (int64_t)cm * cn;
-    if (!plan_part(M, N, K, c, rest, tiles, cus, mode, general, &e)) return WS_OK;
+    if (!plan_part(M, N, K, c, rest, tiles, cus, mode, general, &e)) return;
     e.corner_m = cm;
     e.corner_n = cn;
     e.plan.tiles = (int32_t)tiles;
@@ -312,15 +321,34 @@ ws_status choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, i
     e.plan.rounds = (int32_t)((tiles + e.plan.grid - 1) / e.plan.grid);
     e.plan.xcd_remap = e.plan.grid % 8 == 0;
   } else if (part.tile_m > 0) {
-    if (!plan_part(M, N, K, c, part, tiles_of(M, N, part), cus, mode, general, &run.launch[0])) return WS_OK;
+    if (!plan_part(M, N, K, c, part, tiles_of(M, N, part), cus, mode, general, &run.launch[0])) return;
   } else {
-    return WS_OK;
+    return;
   }
+  *out = run;
+}
+
+// The run of a GEMM (general: by the general kernel) planned without a device:
+// resident workgroups from the compiled kernel's registers, which is what the
+// runtime's occupancy query gives.
+ws_status plan_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int general, bool plain_block,
+                   Run* out) {
+  wsg::PlanOut p;
+  const int s = wsg::plan_launch(plan_in(M, N, K, c, cus, 0, general), &p);
+  if (s != wsg::kPlanOk) return from_plan(s);
+  const wsg::KernelEntry* k = find_kernel(c, 0, wsg::kModeGemm, general);
+  if (!k) return WS_ERR_UNSUPPORTED;
+  *out = whole_run(k->fn, c, general, p);
+  if (p.grid == 0) out->count = 0;  // an empty problem launches no GEMM kernel
+  else choose_run(M, N, K, c, cus, wsg::kModeGemm, general, plain_block, out);
+  return WS_OK;
+}
+
+ws_status allow_lds(const Run& run) {
   for (int i = 0; i < run.count; ++i) {
     const ws_status st = allow_lds(run.launch[i].fn);
     if (st != WS_OK) return st;
   }
-  *out = run;
   return WS_OK;
 }
 
@@ -340,7 +368,7 @@ ws_status launch_run(const Run& run, wsg::KernelArgs a, hipStream_t stream) {
     a.col2 = r.col2;
     a.num_tiles = r.num_tiles;
     a.iters = l.plan.iters;
-    a.stages = l.stages;
+    a.stages = l.cfg.stages;
     a.xcd_remap = l.plan.xcd_remap;
     if (i > 0) a.clock = nullptr;  // one clock sample per run, of its main launch
     void* params[] = {&a};
@@ -363,6 +391,17 @@ void to_info(const wsg::PlanOut& p, ws_gemm_plan_info* o) {
   o->xcd_remap = p.xcd_remap;
   o->ragged = p.ragged;
   o->general = p.ragged;
+}
+
+void to_launches(const Run& run, ws_gemm_launch_info* out, int32_t* count) {
+  *count = run.count;
+  for (int i = 0; i < run.count; ++i) {
+    const Launch& l = run.launch[i];
+    out[i] = ws_gemm_launch_info{l.cfg.tile_m, l.cfg.tile_n, l.cfg.tile_k, l.cfg.stages, l.cfg.producer_waves,
+                                 l.cfg.consumer_waves, l.plan.split, l.general, l.plan.grid, l.plan.block,
+                                 l.plan.lds_bytes, l.plan.tiles_m, l.plan.tiles_n, l.plan.tiles, l.plan.rounds,
+                                 l.plan.iters, l.corner_m < 0 ? 0 : l.corner_m, l.corner_m < 0 ? 0 : l.corner_n};
+  }
 }
 
 bool default_epilogue(const ws_gemm_epilogue& e) {
@@ -424,6 +463,8 @@ struct ws_gemm_handle {
   const wsg::KernelEntry* general; // general twin (partial tiles, epilogue options), or null
   wsg::PlanOut plan_plain, plan_general;  // whole-tile plans of the plain and the general kernel
   Run run_plain, run_general;      // what ws_gemm_run launches for the default / another epilogue
+  Run whole_plain, whole_general;  // the same with every tile whole
+  bool whole;                      // WS_PARTITION_WHOLE is set
   bool use_general;                // another epilogue is set
   ws_gemm_epilogue epi;
   bool calibration;
@@ -433,6 +474,15 @@ struct ws_gemm_handle {
   uint32_t* trace;
   int32_t trace_wgs, trace_iters;
 };
+
+namespace {
+
+const Run& current_run(const ws_gemm_handle* h) {
+  if (h->whole || (h->trace && h->traced)) return h->use_general ? h->whole_general : h->whole_plain;
+  return h->use_general ? h->run_general : h->run_plain;
+}
+
+}  // namespace
 
 extern "C" {
 
@@ -462,6 +512,18 @@ ws_status ws_gemm_plan(int64_t M, int64_t N, int64_t K, const ws_gemm_config* cf
   if (!find_kernel(*cfg, 0, wsg::kModeGemm, p.ragged)) return WS_ERR_UNSUPPORTED;
   to_info(p, out);
   return WS_OK;
+}
+
+ws_status ws_gemm_plan_launches(int64_t M, int64_t N, int64_t K, const ws_gemm_config* cfg, int32_t num_cus,
+                                int32_t general, ws_gemm_launch_info* out, int32_t* count) {
+  if (!cfg || !out || !count) return WS_ERR_INVALID_ARG;
+  wsg::PlanOut p;
+  const int s = wsg::plan_launch(plan_in(M, N, K, *cfg, num_cus, 1), &p);
+  if (s != wsg::kPlanOk) return from_plan(s);
+  Run run;
+  const ws_status st = plan_run(M, N, K, *cfg, num_cus, general || p.ragged, !general, &run);
+  if (st == WS_OK) to_launches(run, out, count);
+  return st;
 }
 
 ws_status ws_gemm_schedule(const ws_gemm_plan_info* info, int32_t wg, int32_t round,
@@ -547,15 +609,19 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   }
 
   // Empty problems launch no GEMM kernel.
-  Run run_plain{{{launch_fn, p, cfg->stages, -1, -1}, {}}, 1};
-  Run run_general{{{general ? general->fn : nullptr, pg, cfg->stages, -1, -1}, {}}, 1};
+  const Run whole_plain = whole_run(launch_fn, *cfg, p.ragged, p);
+  const Run whole_general = whole_run(general ? general->fn : nullptr, *cfg, 1, pg);
+  Run run_plain = whole_plain, run_general = whole_general;
   if (p.grid > 0) {
     const int mode = kind == WS_CALIB_NONE || kind == WS_CALIB_EMPTY ? wsg::kModeGemm : run->mode;
-    ws_status ls = kind == WS_CALIB_EMPTY ? WS_OK
-                                          : choose_run(M, N, K, *cfg, cus, mode, p.ragged, true, &run_plain);
-    if (ls == WS_OK && general)
-      ls = choose_run(M, N, K, *cfg, cus, wsg::kModeGemm, 1, false, &run_general);
-    if (ls != WS_OK) return ls;
+    if (kind != WS_CALIB_EMPTY) {
+      choose_run(M, N, K, *cfg, cus, mode, p.ragged, true, &run_plain);
+      if ((sl = allow_lds(run_plain)) != WS_OK) return sl;
+    }
+    if (general) {
+      choose_run(M, N, K, *cfg, cus, wsg::kModeGemm, 1, false, &run_general);
+      if ((sl = allow_lds(run_general)) != WS_OK) return sl;
+    }
   }
 
   const wsg::KernelEntry* traced = (kind == WS_CALIB_NONE && !p.ragged) ? find_kernel(*cfg, 1) : nullptr;
@@ -574,6 +640,9 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   h->plan_general = pg;
   h->run_plain = run_plain;
   h->run_general = run_general;
+  h->whole_plain = whole_plain;
+  h->whole_general = whole_general;
+  h->whole = false;
   h->use_general = false;
   h->epi = ws_gemm_epilogue{1.0f, 0.0f, WS_OUT_F32};
   h->calibration = kind != WS_CALIB_NONE;
@@ -660,9 +729,8 @@ ws_status ws_gemm_run(ws_gemm_t h, const void* A, const void* B, void* C, hipStr
   a.out_dtype = h->epi.out_dtype;
   a.clock = (unsigned long long*)((char*)h->d_err + kClockOffset);
   // the traced twin runs the whole-tile plan, which its records describe
-  if (h->trace && h->traced)
-    return launch_run(Run{{{h->traced->fn, h->plan, h->cfg.stages, -1, -1}, {}}, 1}, a, stream);
-  return launch_run(h->use_general ? h->run_general : h->run_plain, a, stream);
+  if (h->trace && h->traced) return launch_run(whole_run(h->traced->fn, h->cfg, 0, h->plan), a, stream);
+  return launch_run(current_run(h), a, stream);
 }
 
 ws_status ws_gemm_sync_status(ws_gemm_t h, hipStream_t stream) {
@@ -695,6 +763,19 @@ ws_status ws_gemm_query(ws_gemm_t h, ws_gemm_plan_info* out) {
   if (!h || !out) return WS_ERR_INVALID_ARG;
   to_info(h->plan, out);
   out->general = (h->use_general || h->plan.ragged) ? 1 : 0;
+  return WS_OK;
+}
+
+ws_status ws_gemm_set_partition(ws_gemm_t h, int32_t partition) {
+  if (!h || (partition != WS_PARTITION_AUTO && partition != WS_PARTITION_WHOLE)) return WS_ERR_INVALID_ARG;
+  h->whole = partition == WS_PARTITION_WHOLE;
+  return WS_OK;
+}
+
+ws_status ws_gemm_query_launches(ws_gemm_t h, ws_gemm_launch_info* out, int32_t* count) {
+  if (!h || !out || !count) return WS_ERR_INVALID_ARG;
+  *count = 0;
+  if (h->plan.grid > 0) to_launches(current_run(h), out, count);
   return WS_OK;
 }
 
@@ -793,8 +874,7 @@ ws_status ws_gemm_run_noalloc(int64_t M, int64_t N, int64_t K, const ws_gemm_con
                             dim3(256), params, 0, stream));
     return WS_OK;
   }
-  const wsg::KernelEntry* k = find_kernel(*cfg, 0, wsg::kModeGemm, p.ragged);
-  if (!k) return WS_ERR_UNSUPPORTED;
+  if (!find_kernel(*cfg, 0, wsg::kModeGemm, p.ragged)) return WS_ERR_UNSUPPORTED;
   // The device the launch goes to (the stream's), its scratch and size.
   int dev = 0;
   if (stream) {
@@ -805,13 +885,9 @@ ws_status ws_gemm_run_noalloc(int64_t M, int64_t N, int64_t K, const ws_gemm_con
   StaticDevice sd;
   const ws_status st = static_device(dev, &sd);
   if (st != WS_OK) return st;
-  const ws_status sl = allow_lds(k->fn);
-  if (sl != WS_OK) return sl;
-  // resident workgroups from the compiled kernel's registers: what the runtime's occupancy query gives
-  s = wsg::plan_launch(plan_in(M, N, K, *cfg, sd.cus, 0, p.ragged), &p);
-  if (s != wsg::kPlanOk) return from_plan(s);
-  Run run{{{k->fn, p, cfg->stages, -1, -1}, {}}, 1};
-  const ws_status ls = choose_run(M, N, K, *cfg, sd.cus, wsg::kModeGemm, p.ragged, true, &run);
+  Run run;
+  ws_status ls = plan_run(M, N, K, *cfg, sd.cus, p.ragged, true, &run);
+  if (ls == WS_OK) ls = allow_lds(run);
   if (ls != WS_OK) return ls;
   wsg::KernelArgs a{};
   a.A = (const uint16_t*)A;

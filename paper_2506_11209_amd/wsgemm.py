@@ -64,6 +64,20 @@ class ws_gemm_plan_info(ctypes.Structure):
         return {n: getattr(self, n) for n, _ in self._fields_}
 
 
+# ws_partition
+WS_PARTITION_AUTO, WS_PARTITION_WHOLE = 0, 1
+WS_MAX_LAUNCHES = 2
+
+
+class ws_gemm_launch_info(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in (
+        "tile_m", "tile_n", "tile_k", "stages", "producer_waves", "consumer_waves", "split", "general", "grid",
+        "block", "lds_bytes", "tiles_m", "tiles_n", "tiles", "rounds", "iters", "skip_m", "skip_n")]
+
+    def as_dict(self) -> dict:
+        return {n: getattr(self, n) for n, _ in self._fields_}
+
+
 # ws_out_dtype: element type of C
 WS_OUT_F32, WS_OUT_BF16, WS_OUT_F16 = 0, 1, 2
 OUT_DTYPES = {"f32": WS_OUT_F32, "bf16": WS_OUT_BF16, "f16": WS_OUT_F16}
@@ -129,6 +143,14 @@ _lib.ws_gemm_clock.argtypes = [_h, _p, _u64p, _u64p, ctypes.POINTER(_i64)]
 _lib.ws_gemm_clock.restype = _i32
 _lib.ws_gemm_query.argtypes = [_h, ctypes.POINTER(ws_gemm_plan_info)]
 _lib.ws_gemm_query.restype = _i32
+_launches_p = ctypes.POINTER(ws_gemm_launch_info)
+_lib.ws_gemm_plan_launches.argtypes = [_i64, _i64, _i64, ctypes.POINTER(ws_gemm_config), _i32, _i32, _launches_p,
+                                       ctypes.POINTER(_i32)]
+_lib.ws_gemm_plan_launches.restype = _i32
+_lib.ws_gemm_query_launches.argtypes = [_h, _launches_p, ctypes.POINTER(_i32)]
+_lib.ws_gemm_query_launches.restype = _i32
+_lib.ws_gemm_set_partition.argtypes = [_h, _i32]
+_lib.ws_gemm_set_partition.restype = _i32
 _lib.ws_gemm_set_debug.argtypes = [_h, ctypes.POINTER(ws_gemm_debug)]
 _lib.ws_gemm_set_debug.restype = _i32
 _lib.ws_gemm_set_epilogue.argtypes = [_h, ctypes.POINTER(ws_gemm_epilogue)]
@@ -225,6 +247,23 @@ def ws_gemm_query(h):
     return s, info
 
 
+def ws_gemm_plan_launches(M, N, K, cfg: ws_gemm_config, num_cus: int, general: int = 0):
+    """(status, [ws_gemm_launch_info]) of a run."""
+    out, n = (ws_gemm_launch_info * WS_MAX_LAUNCHES)(), _i32(0)
+    s = _lib.ws_gemm_plan_launches(M, N, K, ctypes.byref(cfg), num_cus, general, out, ctypes.byref(n))
+    return s, list(out[:n.value])
+
+
+def ws_gemm_query_launches(h):
+    out, n = (ws_gemm_launch_info * WS_MAX_LAUNCHES)(), _i32(0)
+    s = _lib.ws_gemm_query_launches(h, out, ctypes.byref(n))
+    return s, list(out[:n.value])
+
+
+def ws_gemm_set_partition(h, partition: int) -> int:
+    return _lib.ws_gemm_set_partition(h, partition)
+
+
 def ws_gemm_set_debug(h, dbg: ws_gemm_debug | None) -> int:
     return _lib.ws_gemm_set_debug(h, ctypes.byref(dbg) if dbg is not None else None)
 
@@ -260,10 +299,12 @@ class WsGemm:
     """A created plan for one (M, N, K, configuration); call it on torch tensors."""
 
     def __init__(self, M, N, K, tile=(128, 128, 32), stages=3, producer_waves=4,
-                 consumer_waves=4, dtype="bf16", load_path="registers", calibration=None, split=0):
+                 consumer_waves=4, dtype="bf16", load_path="registers", calibration=None, split=0, whole_tiles=False):
         """calibration: None for the GEMM, else a key of CALIB_KINDS (the
         calibration kernels of the performance model, same launch).  split:
-        DMA warps per MATH warp (1 or 2; 0 derives it from the wave counts)."""
+        DMA warps per MATH warp (1 or 2; 0 derives it from the wave counts).
+        whole_tiles: run exactly this tile and ring, one launch, never parts
+        of it by other kernels."""
         self.M, self.N, self.K = M, N, K
         self.dtype = dtype
         self.out_dtype = "f32"
@@ -280,6 +321,17 @@ class WsGemm:
         s, self.info = ws_gemm_query(self._h)
         if s != WS_OK:
             raise WsGemmError("ws_gemm_query", s)
+        if whole_tiles:
+            s = ws_gemm_set_partition(self._h, WS_PARTITION_WHOLE)
+            if s != WS_OK:
+                raise WsGemmError("ws_gemm_set_partition", s)
+
+    def launches(self) -> list:
+        """The kernel launches of the next run (ws_gemm_launch_info each)."""
+        s, out = ws_gemm_query_launches(self._h)
+        if s != WS_OK:
+            raise WsGemmError("ws_gemm_query_launches", s)
+        return out
 
     def _check(self, t, shape, dtype_name):
         if t.dtype is not _TORCH_DTYPES[dtype_name] or t.shape != shape or not t.is_cuda or not t.is_contiguous():

@@ -1,9 +1,9 @@
 """Problems whose tiles are computed in parts, or as a block of whole tiles and
 a rest (ws_gemm_run's choice where whole tiles leave the GPU idle): sizes
 around the block's edges, both tile regions of the rest, every entry point.
-Integer operands: every compared element is exact; C is pre-filled with NaN
-and guarded behind its end, so a tile left out or written twice past an edge
-shows."""
+Which launches a case takes is asserted.  Integer operands: every compared
+element is exact; C is pre-filled with NaN and guarded behind its end, so a
+tile left out or written twice past an edge shows."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 T128 = ((128, 128, 64), 3, 4, 4)
 T256 = ((256, 256, 64), 2, 4, 8)
 # (M, N, K), launch, dtype, load path
-CASES = [
+PARTS = [
     # every tile in parts: few whole tiles, ragged ones, both ends of the sizes
     ((1024, 1024, 256), T128, "bf16", "registers"),
     ((128, 128, 64), T128, "bf16", "dma"),
@@ -29,7 +29,9 @@ CASES = [
     ((2048, 512, 128), ((256, 128, 32), 4, 8, 4), "bf16", "registers"),
     ((256, 256, 64), ((64, 64, 32), 2, 1, 1), "f16", "registers"),
     ((100, 72, 200), ((64, 64, 64), 2, 2, 1), "bf16", "registers"),
-    ((1088, 1088, 96), ((64, 64, 32), 4, 1, 1), "bf16", "dma"),
+    ((544, 416, 96), ((64, 64, 32), 4, 1, 1), "bf16", "dma"),
+]
+RESTS = [
     # a block of whole tiles (16 x 16 or more) and the rest below / right / both
     ((2049, 2048, 1280), T128, "bf16", "registers"),
     ((2048, 2056, 1280), T128, "f16", "registers"),
@@ -38,9 +40,10 @@ CASES = [
     ((2048, 2176, 1280), ((128, 128, 32), 3, 8, 4), "bf16", "registers"),
     ((4100, 4104, 264), T256, "bf16", "registers"),
     ((4100, 4104, 1288), T256, "f16", "registers"),
-    ((5000, 2568, 1280), ((256, 128, 64), 3, 4, 4), "bf16", "registers"),
+    ((4100, 2056, 1280), ((256, 128, 64), 3, 4, 4), "bf16", "registers"),
     ((1100, 1032, 5120), ((64, 64, 64), 3, 1, 1), "bf16", "registers"),
 ]
+CASES = [c + (1,) for c in PARTS] + [c + (2,) for c in RESTS]
 GUARD, SENTINEL = 4096, -7.0
 
 
@@ -56,8 +59,12 @@ def check(C, A, B, dtype, tm, scale=1.0):
     assert r["ok"], r
 
 
-@pytest.mark.parametrize("shape,launch,dtype,path", CASES, ids=str)
-def test_partitioned_products_are_exact(shape, launch, dtype, path):
+def tile_of(launch):
+    return launch.tile_m, launch.tile_n, launch.tile_k
+
+
+@pytest.mark.parametrize("shape,launch,dtype,path,count", CASES, ids=str)
+def test_partitioned_products_are_exact(shape, launch, dtype, path, count):
     M, N, K = shape
     tile, P, np_, nc = launch
     log("case partition %s %s %s %s" % (shape, launch, dtype, path))
@@ -65,6 +72,11 @@ def test_partitioned_products_are_exact(shape, launch, dtype, path):
     Ad, Bd = A.cuda(), B.cuda()
     g = w.WsGemm(M, N, K, tile, P, np_, nc, dtype, path)
     try:
+        ls = g.launches()
+        assert len(ls) == count and tile_of(ls[-1]) != tile  # in parts, or a block and the rest in parts
+        assert count == 1 or tile_of(ls[0]) == tile
+        _, planned = w.ws_gemm_plan_launches(M, N, K, g.cfg, torch.cuda.get_device_properties(0).multi_processor_count)
+        assert [x.as_dict() for x in planned] == [x.as_dict() for x in ls]
         buf = torch.full((M * N + GUARD,), float("nan"), device="cuda")
         buf[M * N:] = SENTINEL
         st = torch.cuda.current_stream().cuda_stream
@@ -87,6 +99,15 @@ def test_partitioned_products_are_exact(shape, launch, dtype, path):
         again = g(Ad, Bd)
         torch.cuda.synchronize()
         assert np.array_equal(again.cpu().numpy().view(np.uint32), C.view(np.uint32))
+        # whole tiles, by the requested kernel and ring: the same bits
+        assert w.ws_gemm_set_partition(g._h, w.WS_PARTITION_WHOLE) == w.WS_OK
+        one, = g.launches()
+        assert tile_of(one) == tile and one.stages == P and one.consumer_waves == nc and one.grid == g.info.grid
+        again = g(Ad, Bd, torch.full((M, N), float("nan"), device="cuda"))
+        assert g.sync_status() == w.WS_OK
+        assert np.array_equal(again.cpu().numpy().view(np.uint32), C.view(np.uint32))
+        assert w.ws_gemm_set_partition(g._h, w.WS_PARTITION_AUTO) == w.WS_OK and len(g.launches()) == count
+        assert w.ws_gemm_set_partition(g._h, 2) == w.WS_ERR_INVALID_ARG
     finally:
         g.close()
 
@@ -101,6 +122,8 @@ def test_synchronous_parts_are_exact(shape, tile, P, nc):
     A, B = inputs.make_operands(M, N, K, "bf16", "int4", M + K)
     g = w.WsGemm(M, N, K, tile, P, 0, nc, "bf16")
     try:
+        part, = g.launches()
+        assert tile_of(part) != tile and part.stages == P
         C = torch.full((M, N), float("nan"), device="cuda")
         g(A.cuda(), B.cuda(), C)
         assert g.sync_status() == w.WS_OK
@@ -116,6 +139,7 @@ def test_two_launch_run_under_capture_and_the_launch_clock():
     Ad, Bd = A.cuda(), B.cuda()
     g = w.WsGemm(M, N, K, T128[0], T128[1], T128[2], T128[3], "bf16")
     try:
+        assert len(g.launches()) == 2
         eager = g(Ad, Bd)
         torch.cuda.synchronize()
         assert g.clock_mhz()[1] == 1  # one sample per run
