@@ -33,9 +33,8 @@
  * same to the bit (every element takes its products in the same order), and
  * the plan a handle reports stays that of its whole tiles.  A block of whole
  * tiles may also run first and the rest, in parts, as a second launch of the
- * same run.  Calibration kernels (except the empty one) take parts likewise,
- * always in one launch; traced runs take whole tiles.  ws_gemm_query_launches
- * reports what a run launches, ws_gemm_set_partition keeps a handle to the
+ * same run.  Calibration kernels and traced runs always take whole tiles, as the
+ * plan counts them.  ws_gemm_query_launches reports what a run launches, ws_gemm_set_partition keeps a handle to the
  * requested tile and ring.
  *
  * Data layout: A, B and C are dense and row-major (leading dimensions K, N
@@ -275,7 +274,8 @@ ws_status ws_gemm_set_trace(ws_gemm_t h, void* buffer, int64_t bytes, int32_t wg
  * the Kernel Launch Time", "Measure the Epilogue Time", "Estimate the
  * Throughput and Startup Latency of the DMA and MATH Warps").  Each is the
  * GEMM kernel of cfg with one role reduced, launched with the GEMM's own
- * plan (grid, block, LDS ring), so it measures that kernel's costs:
+ * plan of whole tiles (grid, block, LDS ring; a GEMM handle set to
+ * WS_PARTITION_WHOLE), so it measures that kernel's costs:
  *   WS_CALIB_EMPTY     an empty kernel with the same launch (T_INIT);
  *   WS_CALIB_LOAD_A    producers load only the A tiles of every K-iteration
  *                      into the ring; consumers free each slot unread;

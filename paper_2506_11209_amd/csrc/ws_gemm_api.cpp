@@ -218,14 +218,14 @@ ws_gemm_config part_of(const ws_gemm_config& c, int tm, int tn) {
 // only: its one loading wave takes 390 ns for 64 of K, four loading waves 280 ns
 // for a 64 x 64 tile (48x4096x4096: 256 such parts 28.9 us, 64 tiles 22.9 us).
 template <typename Count, typename F>
-void each_part(const ws_gemm_config& c, int cus, int mode, int general, int64_t limit, Count count, F f) {
+void each_part(const ws_gemm_config& c, int cus, int general, int64_t limit, Count count, F f) {
   const int least = c.consumer_waves == 1 ? 32 : 64;
   for (int tm = c.tile_m; tm >= least; tm /= 2)
     for (int tn = c.tile_n; tn >= least; tn /= 2) {
       if (tm == c.tile_m && tn == c.tile_n) continue;
       const ws_gemm_config k = part_of(c, tm, tn);
       const int64_t cost = wsg::tiles_cost(count(k), tm, tn, cus);
-      if (cost < limit && find_kernel(k, 0, mode, general)) {
+      if (cost < limit && find_kernel(k, 0, wsg::kModeGemm, general)) {
         f(k, cost);
         limit = cost;
       }
@@ -243,17 +243,17 @@ int per_cu(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
 
 // Plan of `tiles` tiles of part k of c on the M x N x K problem.
 bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm_config k, int64_t tiles, int cus,
-               int mode, int general, Launch* l) {
+               int general, Launch* l) {
   if (c.producer_waves > 0)  // the synchronous kernel's depth says whether it overlaps: kept
     k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n),
                                 2ll * c.tile_k * (k.tile_m + k.tile_n), per_cu(k, general, tiles, cus));
   wsg::PlanOut plan;
   if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0, general), &plan) != wsg::kPlanOk) return false;
-  *l = Launch{find_kernel(k, 0, mode, general)->fn, k, general, plan, -1, -1};
+  *l = Launch{find_kernel(k, 0, wsg::kModeGemm, general)->fn, k, general, plan, -1, -1};
   return true;
 }
 
-// Chooses how to compute the problem with the kernel (mode, general) of c:
+// Chooses how to compute the problem with the (general) kernel of c:
 // whole tiles (as `out` comes in), every tile in parts, or a block of whole
 // tiles and, in a second launch, the rest in parts - the rest being partial
 // edge tiles, which would multiply padding for a round of their own, or what a
@@ -264,21 +264,21 @@ bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm
 // Measured, whole tiles -> block and rest: 4100x4104x4104 with 256x256x64 tiles
 // (289 tiles, 33 of them almost all padding) 199 -> 148 us, as 128x128 parts
 // 269 us.
-void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int mode, int general,
-                bool plain_block, Run* out) {
+void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int general, bool plain_block,
+                Run* out) {
   const Launch& whole = out->launch[0];
   // costs of the whole problem: part_cost units are ns per 64 of K
   const int64_t slabs = (K + 63) / 64;
   const int64_t whole_cost = wsg::tiles_cost(whole.plan.tiles, c.tile_m, c.tile_n, cus) * slabs;
   int64_t best = whole_cost * 10 / 11;  // what another partition must not exceed
   ws_gemm_config part{}, rest{};
-  each_part(c, cus, mode, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
+  each_part(c, cus, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
             [&](const ws_gemm_config& k, int64_t cost) {
               part = k;
               best = cost * slabs;
             });
   int rows_best = 0, cols_best = 0;
-  if (mode == wsg::kModeGemm && c.producer_waves > 0) {
+  if (c.producer_waves > 0) {
     const int64_t rows = M / c.tile_m, cols = N / c.tile_n, rounds = rows * cols / cus;
     for (int t = 0; t < 3 && rows > 0 && cols > 0; ++t) {
       // all whole tiles, or as many rows (columns) of them as whole rounds hold
@@ -286,7 +286,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
       if (r < 1 || q < 1 || (r * c.tile_m >= M && q * c.tile_n >= N)) continue;
       const int64_t block = wsg::tiles_cost(r * q, c.tile_m, c.tile_n, cus) * slabs + wsg::kSecondLaunchNs;
       if (block >= best) continue;
-      each_part(c, cus, mode, general, (best - block) / slabs,
+      each_part(c, cus, general, (best - block) / slabs,
                 [&](const ws_gemm_config& k) {
                   return tiles_of(M, N, k) - r * q * (c.tile_m / k.tile_m) * (c.tile_n / k.tile_n);
                 },
@@ -306,14 +306,14 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
     if (wsg::plan_launch(plan_in((int64_t)rows_best * c.tile_m, (int64_t)cols_best * c.tile_n, K, c, cus, 0),
                          &m.plan) != wsg::kPlanOk)
       return;
-    const wsg::KernelEntry* plain = plain_block && K % c.tile_k == 0 ? find_kernel(c, 0, mode, 0) : nullptr;
+    const wsg::KernelEntry* plain = plain_block && K % c.tile_k == 0 ? find_kernel(c, 0, wsg::kModeGemm, 0) : nullptr;
     if (plain) {
       m.fn = plain->fn;
       m.general = 0;
     }
     const int cm = rows_best * (c.tile_m / rest.tile_m), cn = cols_best * (c.tile_n / rest.tile_n);
     const int64_t tiles = tiles_of(M, N, rest) - (int64_t)cm * cn;
-    if (!plan_part(M, N, K, c, rest, tiles, cus, mode, general, &e)) return;
+    if (!plan_part(M, N, K, c, rest, tiles, cus, general, &e)) return;
     e.corner_m = cm;
     e.corner_n = cn;
     e.plan.tiles = (int32_t)tiles;
@@ -321,7 +321,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
     e.plan.rounds = (int32_t)((tiles + e.plan.grid - 1) / e.plan.grid);
     e.plan.xcd_remap = e.plan.grid % 8 == 0;
   } else if (part.tile_m > 0) {
-    if (!plan_part(M, N, K, c, part, tiles_of(M, N, part), cus, mode, general, &run.launch[0])) return;
+    if (!plan_part(M, N, K, c, part, tiles_of(M, N, part), cus, general, &run.launch[0])) return;
   } else {
     return;
   }
@@ -340,7 +340,7 @@ ws_status plan_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int
   if (!k) return WS_ERR_UNSUPPORTED;
   *out = whole_run(k->fn, c, general, p);
   if (p.grid == 0) out->count = 0;  // an empty problem launches no GEMM kernel
-  else choose_run(M, N, K, c, cus, wsg::kModeGemm, general, plain_block, out);
+  else choose_run(M, N, K, c, cus, general, plain_block, out);
   return WS_OK;
 }
 
@@ -612,14 +612,12 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   const Run whole_plain = whole_run(launch_fn, *cfg, p.ragged, p);
   const Run whole_general = whole_run(general ? general->fn : nullptr, *cfg, 1, pg);
   Run run_plain = whole_plain, run_general = whole_general;
-  if (p.grid > 0) {
-    const int mode = kind == WS_CALIB_NONE || kind == WS_CALIB_EMPTY ? wsg::kModeGemm : run->mode;
-    if (kind != WS_CALIB_EMPTY) {
-      choose_run(M, N, K, *cfg, cus, mode, p.ragged, true, &run_plain);
-      if ((sl = allow_lds(run_plain)) != WS_OK) return sl;
-    }
+  // Calibration kernels take the whole tiles that the plan they report counts.
+  if (p.grid > 0 && kind == WS_CALIB_NONE) {
+    choose_run(M, N, K, *cfg, cus, p.ragged, true, &run_plain);
+    if ((sl = allow_lds(run_plain)) != WS_OK) return sl;
     if (general) {
-      choose_run(M, N, K, *cfg, cus, wsg::kModeGemm, 1, false, &run_general);
+      choose_run(M, N, K, *cfg, cus, 1, false, &run_general);
       if ((sl = allow_lds(run_general)) != WS_OK) return sl;
     }
   }

@@ -64,6 +64,34 @@ def test_calibration_at_bench_launch(kind):
         assert bool((C == 0).all())
 
 
+@pytest.mark.parametrize("kind", ["empty", "load_a", "load_b", "math", "epilogue", "load_ab"])
+@pytest.mark.parametrize("tile,stages,np_,nc,split,M,N,K", [
+    ((128, 128, 64), 3, 4, 4, 1, 1024, 1024, 512),     # few tiles: the GEMM itself runs parts
+    ((256, 256, 64), 2, 4, 8, 2, 2048, 2048, 512),
+    ((128, 128, 64), 3, 4, 4, 1, 2176, 2048, 1280),    # the GEMM runs a block and the rest
+])
+def test_calibration_runs_the_plan_it_reports(tile, stages, np_, nc, split, M, N, K, kind):
+    """T_INIT, T_EPILOGUE and the costs per K-iteration are differences and
+    quotients over the plan's rounds and grid: every kind launches that plan."""
+    log("calibration launch %s %s" % (kind, tile))
+    gemm = w.WsGemm(M, N, K, tile, stages, np_, nc, "bf16", split=split)
+    g = w.WsGemm(M, N, K, tile, stages, np_, nc, "bf16", calibration=kind, split=split)
+    try:
+        assert gemm.launches()[-1].tile_m < tile[0]
+        launch, = g.launches()
+        assert (launch.tile_m, launch.tile_n, launch.tile_k) == tile and launch.stages == stages
+        assert (launch.grid, launch.rounds, launch.tiles) == (g.info.grid, g.info.rounds, g.info.tiles)
+        assert w.ws_gemm_set_partition(gemm._h, w.WS_PARTITION_WHOLE) == w.WS_OK
+        assert gemm.launches()[0].as_dict() == launch.as_dict()
+        A = torch.zeros(M, K, device="cuda", dtype=torch.bfloat16)
+        B = torch.zeros(K, N, device="cuda", dtype=torch.bfloat16)
+        g(A, B, torch.zeros(M, N, device="cuda"))
+        assert g.sync_status() == w.WS_OK
+    finally:
+        g.close()
+        gemm.close()
+
+
 def test_calibration_handles_refuse_tracing():
     g = w.WsGemm(512, 512, 512, (128, 128, 64), 3, 4, 4, "bf16", calibration="math")
     try:
