@@ -219,6 +219,13 @@ def main():
     sm = summary(dev)
     value = wl.flops / (wall_ms * 1e-3) / 1e12
     pkey = point_key(point) + "/" + a.load_path
+    # the kernel that ran: a problem of few tiles takes another than the point's own
+    ran = g.launches()
+    own = len(ran) == 1 and (ran[0].tile_m, ran[0].tile_n, ran[0].stages) == (tm, tn, stages)
+    kernel = " + ".join(
+        "ws_gemm_kernel<%d,%d,%d,%d,%d,%d,%s>" % (l.tile_m, l.tile_n, l.tile_k, l.consumer_waves, l.producer_waves,
+                                                  l.split, wl.dtype) if np_ > 0 else
+        "ws_sync_kernel<%d,%d,%d,%d,%s>" % (l.tile_m, l.tile_n, l.tile_k, l.consumer_waves, wl.dtype) for l in ran)
     # roofline of the kernel: MFMA peak, or HBM bandwidth below the ridge point
     if wl.flops / wl.bytes >= PEAK_TFLOPS * 1e12 / (PEAK_HBM_GBS * 1e9):
         bound, unit, peak = "mfma", "TFLOP/s", PEAK_TFLOPS
@@ -250,10 +257,8 @@ def main():
                    "load_path": a.load_path, "grid": g.info.grid, "rounds": g.info.rounds},
         "roofline": {"bound": bound, "achieved": round(achieved, 2), "peak": peak,
                      "unit": unit, "frac": round(achieved / peak, 4),
-                     "traffic": traffic_for(pkey, point, wl.dtype, wl.name) if np_ > 0 else None,
-                     "kernel": ("ws_gemm_kernel<%d,%d,%d,%d,%d,%d,%s>" % (tm, tn, tk, nc, np_, split_of(point),
-                                                                          wl.dtype)
-                                if np_ > 0 else "ws_sync_kernel<%d,%d,%d,%d,%s>" % (tm, tn, tk, nc, wl.dtype)),
+                     "traffic": traffic_for(pkey, point, wl.dtype, wl.name) if np_ > 0 and own else None,
+                     "kernel": kernel,
                      "algorithmic_bytes": wl.bytes, "flop": wl.flops,
                      "achieved_at_median": round(achieved * sm["mean_ms"] / sm["median_ms"], 2),
                      "launch_ms": {k: round(v, 5) if isinstance(v, float) else v for k, v in sm.items()},

@@ -8,7 +8,8 @@ predicts each time with the calibrated model (library ``ws_model_predict``)
 and reports the relative error |predicted - measured| / measured: its mean
 and maximum over the grid, the paper's two accuracy figures.  Two readings of
 the schedule are evaluated side by side: the per-round pipeline the paper
-prints (Section 2.1/2.2) and the persistent grid the kernel runs.
+prints (Section 2.1/2.2) and the persistent grid the kernel runs.  Every launch
+takes whole tiles, which is what the model describes.
 
 Grids:
   accuracy  M, N in {2048, 4096, 8192}, K in {1024, 4096, 8192}, tiles
@@ -108,7 +109,7 @@ def main(argv=None):
     rows = []
     fout = open(a.out, "w") if a.out else None
     for (M, N, K, tile, P, split) in grid:
-        g = w.WsGemm(M, N, K, tile, P, 4 * split, 4, "bf16", a.load_path)
+        g = w.WsGemm(M, N, K, tile, P, 4 * split, 4, "bf16", a.load_path, whole_tiles=True)
         try:
             ap_, bp, cp = A.data_ptr(), B.data_ptr(), C.data_ptr()
             dev, _ = time_launches(lambda: g.run_ptrs(ap_, bp, cp, st), a.steps, a.warmup)

@@ -54,7 +54,7 @@ def measure(rows, M, N, K, load_path, steps, warmup):
 
     def median_us(r, nsteps, nwarm, min_seconds=0.0):
         g = w.WsGemm(M, N, K, r["tile"], r["stages"], r["producer_waves"], r["consumer_waves"], "bf16",
-                     load_path, split=r["split"])
+                     load_path, split=r["split"], whole_tiles=True)
         try:
             t0 = time.perf_counter()
             while True:

@@ -42,6 +42,7 @@ def measure_point(wl, point, Ad, Bd, C, steps, warmup, load_path="registers", mi
         rec["status"] = w.ws_gemm_status_str(s)
         return rec
     try:
+        w.ws_gemm_set_partition(h, w.WS_PARTITION_WHOLE)  # this point's own kernel and ring
         _, info = w.ws_gemm_query(h)
         stream = torch.cuda.current_stream().cuda_stream
         a, b, c = Ad.data_ptr(), Bd.data_ptr(), C.data_ptr()

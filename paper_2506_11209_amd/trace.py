@@ -38,7 +38,8 @@ def run_traced(wl, point, wgs=4, Ad=None, Bd=None, load_path="registers", warmup
     if Ad is None:
         A, B = inputs.make_operands(wl.M, wl.N, wl.K, wl.dtype, wl.dist, wl.seed)
         Ad, Bd = A.cuda(), B.cuda()
-    g = w.WsGemm(wl.M, wl.N, wl.K, (tm, tn, tk), stages, np_, nc, wl.dtype, load_path, split=split)
+    g = w.WsGemm(wl.M, wl.N, wl.K, (tm, tn, tk), stages, np_, nc, wl.dtype, load_path, split=split,
+                 whole_tiles=True)  # a traced run takes whole tiles, and so does the untraced one it is compared with
     try:
         wgs = min(wgs, g.info.grid)
         iters = g.info.rounds * g.info.iters

@@ -74,6 +74,7 @@ def measure(name, shape, epi, steps, warmup, point=DEFAULT_POINT):
         s = summary(dev)
         return {"case": name, "point": "x".join(map(str, point)), "M": M, "N": N, "K": K, "alpha": alpha,
                 "beta": beta, "out_dtype": out,
+                "launches": [[l.tile_m, l.tile_n, l.tile_k, l.tiles] for l in g.launches()],
                 "general": g.info.general, "ragged": g.info.ragged, "grid": g.info.grid,
                 "mean_ms": round(s["mean_ms"], 5), "median_ms": round(s["median_ms"], 5),
                 "tflops": round(2.0 * M * N * K / (s["median_ms"] * 1e-3) / 1e12, 1)}

@@ -92,6 +92,44 @@ def test_calibration_runs_the_plan_it_reports(tile, stages, np_, nc, split, M, N
         gemm.close()
 
 
+def test_tools_measure_the_launch_point_they_name(monkeypatch, tmp_path):
+    """The sweep, the optimizer, the model's evaluation and the event trace time
+    the tile and ring they report (and predict) also where a run would take
+    parts; the benchmark's line names the kernel that ran."""
+    import json
+
+    from paper_2506_11209_amd import model_eval, optimize, sweep, trace
+    from paper_2506_11209_amd.workloads import Workload
+    seen = []
+    run = w.ws_gemm_run
+
+    def spy(h, *a):
+        seen.append([(l.tile_m, l.tile_n, l.tile_k, l.stages) for l in w.ws_gemm_query_launches(h)[1]])
+        return run(h, *a)
+
+    monkeypatch.setattr(w, "ws_gemm_run", spy)
+    point = (128, 128, 64, 3, 4, 4)
+    wl = Workload("few_tiles", 512, 512, 256, "bf16", "normal", 1, False, (point,))
+    A = torch.randn(512, 256, device="cuda").bfloat16()
+    B = torch.randn(256, 512, device="cuda").bfloat16()
+    log("case tools sweep")
+    assert sweep.measure_point(wl, point, A, B, torch.empty(512, 512, device="cuda"), 2, 1,
+                               min_warmup_s=0.0)["status"] == "ok"
+    log("case tools optimizer")
+    optimize.measure([{"tile": (128, 128, 64), "stages": 3, "producer_waves": 4, "consumer_waves": 4, "split": 1,
+                       "time_us": 1.0}], 512, 512, 256, "registers", 2, 1)
+    log("case tools trace")
+    trace.run_traced(wl, point, wgs=1, Ad=A, Bd=B)
+    log("case tools model")
+    params = dict(t_init=1.0, t_epilogue=1.0, compute_throughput=1.0, compute_latency=1.0, load_throughput=1.0,
+                  load_latency=1.0)
+    calib = tmp_path / "calib.json"
+    calib.write_text(json.dumps({"calibrations": [{"split": 1, "load_path": "registers", "params": params}]}))
+    monkeypatch.setattr(model_eval, "paper_grid", lambda: [(512, 512, 256, (128, 128, 64), 3, 1)])
+    model_eval.main(["--calib", str(calib), "--grid", "paper", "--steps", "2", "--warmup", "1", "--fixed", "launch"])
+    assert len(seen) > 12 and all(x == [(128, 128, 64, 3)] for x in seen), seen
+
+
 def test_calibration_handles_refuse_tracing():
     g = w.WsGemm(512, 512, 512, (128, 128, 64), 3, 4, 4, "bf16", calibration="math")
     try:
