@@ -16,9 +16,28 @@ def log(msg: str) -> None:
     print(msg, flush=True)
 
 
+def whole_then_auto(g, call):
+    """call(), the output of one run of handle g as a new numpy array, computed by
+    exactly the handle's tile, waves and ring; where the library by itself would
+    take other kernels, by those too, to the same bits."""
+    from paper_2506_11209_amd import wsgemm as w
+    assert w.ws_gemm_set_partition(g._h, w.WS_PARTITION_WHOLE) == w.WS_OK
+    own, = g.launches()
+    c = g.cfg
+    assert (own.tile_m, own.tile_n, own.tile_k, own.stages, own.producer_waves, own.consumer_waves) == (
+        c.tile_m, c.tile_n, c.tile_k, c.stages, c.producer_waves, c.consumer_waves)
+    out = call()
+    assert w.ws_gemm_set_partition(g._h, w.WS_PARTITION_AUTO) == w.WS_OK
+    if [l.as_dict() for l in g.launches()] != [own.as_dict()]:
+        other = call()
+        assert other.tobytes() == out.tobytes(), "parts of the tile give another result"
+    return out
+
+
 def run_gpu(A_cpu, B_cpu, tile, stages, np_, nc, dtype, C_fill=float("nan"), repeats=1,
             load_path="registers", split=0):
-    """C = A B through the library on cuda:0; returns the last C as float32 numpy."""
+    """C = A B through the library on cuda:0, by the requested kernel and by the
+    launches the library takes; returns the last C as float32 numpy."""
     from paper_2506_11209_amd import wsgemm as w
     M, K = A_cpu.shape
     N = B_cpu.shape[1]
@@ -26,12 +45,16 @@ def run_gpu(A_cpu, B_cpu, tile, stages, np_, nc, dtype, C_fill=float("nan"), rep
     try:
         A = A_cpu.cuda()
         B = B_cpu.cuda()
-        C = torch.full((M, N), C_fill, dtype=torch.float32, device="cuda")
-        for _ in range(repeats):
-            g(A, B, C)
-        st = g.sync_status()
-        assert st == w.WS_OK, w.ws_gemm_status_str(st)
-        return C.cpu().numpy()
+
+        def call():
+            C = torch.full((M, N), C_fill, dtype=torch.float32, device="cuda")
+            for _ in range(repeats):
+                g(A, B, C)
+            st = g.sync_status()
+            assert st == w.WS_OK, w.ws_gemm_status_str(st)
+            return C.cpu().numpy()
+
+        return whole_then_auto(g, call)
     finally:
         g.close()
 

@@ -63,7 +63,7 @@ def run_and_check(M, N, K, tile, stages, dtype="bf16", load_path="registers", de
                   nc=4, np_=None):
     A, B = inputs.make_operands(M, N, K, dtype, "int4", seed)
     np_ = 4 * split if np_ is None else np_
-    g = w.WsGemm(M, N, K, tile, stages, np_, nc, dtype, load_path, split=split)
+    g = w.WsGemm(M, N, K, tile, stages, np_, nc, dtype, load_path, split=split, whole_tiles=True)
     try:
         info = g.info.as_dict()
         if debug:
@@ -123,7 +123,7 @@ def test_late_producers_and_consumer_delay_eight_consumers(pdelay, cdelay, split
 def test_watchdog_eight_consumers():
     A, B = inputs.make_operands(1024, 512, 1024, "bf16", "int4", 18)
     log("case roll watchdog")
-    g = w.WsGemm(1024, 512, 1024, (256, 256, 64), 2, 4, 8, "bf16")
+    g = w.WsGemm(1024, 512, 1024, (256, 256, 64), 2, 4, 8, "bf16", whole_tiles=True)
     try:
         Ad, Bd = A.cuda(), B.cuda()
         g.set_debug(1, 20, 0)  # one poll allowed, producers ~160k cycles late
@@ -142,7 +142,7 @@ def test_watchdog_eight_consumers():
 def test_watchdog_reports_timeout_then_recovers():
     A, B = inputs.make_operands(1024, 512, 1024, "bf16", "int4", 17)
     log("case deep watchdog")
-    g = w.WsGemm(1024, 512, 1024, (256, 128, 64), 3, 4, 4, "bf16")
+    g = w.WsGemm(1024, 512, 1024, (256, 128, 64), 3, 4, 4, "bf16", whole_tiles=True)
     try:
         Ad, Bd = A.cuda(), B.cuda()
         g.set_debug(1, 20, 0)  # one poll allowed, producers ~160k cycles late

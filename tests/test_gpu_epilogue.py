@@ -15,7 +15,7 @@ import oracle
 from oracle import epilogue_ref as E
 from oracle.check import compare_exact
 from paper_2506_11209_amd import inputs
-from tests.gpu_helpers import log
+from tests.gpu_helpers import log, whole_then_auto
 
 w = pytest.importorskip("paper_2506_11209_amd.wsgemm")
 
@@ -45,13 +45,17 @@ def run_epilogue(A, B, C_in, launch, alpha, beta, out):
         # the default epilogue keeps the plain kernel on whole tiles
         default = (alpha, beta, out) == (1.0, 0.0, "f32")
         assert g.info.general == (0 if default and not g.info.ragged else 1)
-        buf = torch.full((M * N + GUARD,), SENTINEL, dtype=TORCH_OUT[out])
-        buf[:M * N] = C_in.reshape(-1)
-        buf = buf.cuda()
         Ad, Bd = A.cuda(), B.cuda()
-        g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), buf.data_ptr(), torch.cuda.current_stream().cuda_stream)
-        assert g.sync_status() == w.WS_OK
-        res = buf.cpu().to(torch.float64).numpy()
+
+        def call():
+            buf = torch.full((M * N + GUARD,), SENTINEL, dtype=TORCH_OUT[out])
+            buf[:M * N] = C_in.reshape(-1)
+            buf = buf.cuda()
+            g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), buf.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            assert g.sync_status() == w.WS_OK
+            return buf.cpu().to(torch.float64).numpy()
+
+        res = whole_then_auto(g, call)
         return res[:M * N].reshape(M, N), res[M * N:]
     finally:
         g.close()

@@ -1,7 +1,8 @@
 """Seeded random cases over every compiled specialised configuration: random
 shapes (whole or ragged tiles, down to a single row), ring depths, load paths
 and epilogues, on small-integer operands so that every case must match the
-oracle bit for bit.  Each case prints its parameters before it runs."""
+oracle bit for bit, by the configuration's own kernel and by the launches the
+library takes.  Each case prints its parameters before it runs."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,7 @@ from oracle import epilogue_ref as E
 from oracle.check import compare_exact
 from paper_2506_11209_amd import inputs
 from paper_2506_11209_amd.build import MODE_GEMM, instances
-from tests.gpu_helpers import log
+from tests.gpu_helpers import log, whole_then_auto
 
 w = pytest.importorskip("paper_2506_11209_amd.wsgemm")
 
@@ -60,13 +61,17 @@ def test_random_case_is_exact(i):
                  split=c["split"])
     try:
         g.set_epilogue(alpha, beta, out)
-        buf = torch.full((M * N + GUARD,), SENTINEL, dtype=TORCH_OUT[out])
-        buf[:M * N] = C_in.reshape(-1)
-        buf = buf.cuda()
         Ad, Bd = A.cuda(), B.cuda()
-        g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), buf.data_ptr(), torch.cuda.current_stream().cuda_stream)
-        assert g.sync_status() == w.WS_OK
-        res = buf.cpu().to(torch.float64).numpy()
+
+        def call():
+            buf = torch.full((M * N + GUARD,), SENTINEL, dtype=TORCH_OUT[out])
+            buf[:M * N] = C_in.reshape(-1)
+            buf = buf.cuda()
+            g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), buf.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            assert g.sync_status() == w.WS_OK
+            return buf.cpu().to(torch.float64).numpy()
+
+        res = whole_then_auto(g, call)
     finally:
         g.close()
     assert np.all(res[M * N:] == SENTINEL), "wrote past the end of C"
@@ -96,11 +101,15 @@ def test_random_synchronous_case_is_exact(i):
     A, B = inputs.make_operands(M, N, K, dtype, "int4", 9500 + i)
     g = w.WsGemm(M, N, K, (tm, tn, tk), stages, 0, nc, dtype)
     try:
-        buf = torch.full((M * N + GUARD,), SENTINEL, device="cuda")
         Ad, Bd = A.cuda(), B.cuda()
-        g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), buf.data_ptr(), torch.cuda.current_stream().cuda_stream)
-        assert g.sync_status() == w.WS_OK
-        res = buf.cpu().numpy()
+
+        def call():
+            buf = torch.full((M * N + GUARD,), SENTINEL, device="cuda")
+            g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), buf.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            assert g.sync_status() == w.WS_OK
+            return buf.cpu().numpy()
+
+        res = whole_then_auto(g, call)
     finally:
         g.close()
     assert np.all(res[M * N:] == SENTINEL)

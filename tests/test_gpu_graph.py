@@ -1,7 +1,7 @@
 """ws_gemm_run under HIP graph capture and on concurrent streams.
 
-A run is one kernel launch on the caller's stream (no memset, no
-allocation), so it can be captured: the captured launch is replayed several
+A run is one kernel launch on the caller's stream, or two (no memset, no
+allocation), so it can be captured: the captured run is replayed several
 times, with eager launches and synchronisations of the program in between,
 and every replay must equal the eager result bit for bit.  Two handles on two
 streams must not disturb each other."""
@@ -16,22 +16,23 @@ w = pytest.importorskip("paper_2506_11209_amd.wsgemm")
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("whole", [True, False], ids=["whole", "auto"])
 @pytest.mark.parametrize("shape,tile,stages,np_,nc,epi", [
     ((512, 512, 512), (128, 128, 32), 3, 4, 4, None),                # plain kernel
     ((300, 264, 200), (256, 128, 64), 3, 4, 4, (0.5, 1.0, "bf16")),  # general variant, reads C
     ((256, 256, 0), (128, 128, 32), 3, 4, 4, (1.0, 2.0, "f32")),     # K = 0: the scale kernel
-    ((1024, 1024, 448), (256, 128, 64), 3, 4, 4, None),             # deep-prefetch consumer
+    ((1024, 1024, 448), (256, 128, 64), 3, 4, 4, None),             # large wave tiles
     ((1024, 512, 512), (128, 64, 64), 4, 8, 4, None),               # the same, 2:1
 ], ids=["plain", "general", "k0", "deep", "deep-2to1"])
-def test_captured_run_replays_equal_eager(shape, tile, stages, np_, nc, epi):
+def test_captured_run_replays_equal_eager(shape, tile, stages, np_, nc, epi, whole):
     M, N, K = shape
-    log("case graph %s %s" % (shape, epi))
+    log("case graph %s %s whole=%s" % (shape, epi, whole))
     out = epi[2] if epi else "f32"
     dt = {"f32": torch.float32, "bf16": torch.bfloat16}[out]
     A, B = inputs.make_operands(M, N, K, "bf16", "int4", 61)
     C0 = inputs.make_output(M, N, out, "int4", 62).cuda()
     Ad, Bd = A.cuda(), B.cuda()
-    g = w.WsGemm(M, N, K, tile, stages, np_, nc, "bf16")
+    g = w.WsGemm(M, N, K, tile, stages, np_, nc, "bf16", whole_tiles=whole)
     try:
         if epi:
             g.set_epilogue(*epi)

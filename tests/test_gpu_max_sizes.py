@@ -4,8 +4,8 @@ kernel's address arithmetic, in the benchmark's launch configuration
 
   * K at the A-panel limit (256 K 2 bytes just below 2^31): 65535
     K-iterations through one tile, with a partial tile (general variant) and
-    with one whole tile (plain kernel, deep-prefetch consumer); also through
-    four 128x64 tiles of the two-producer-group (2:1) deep-prefetch kernel;
+    with one whole tile (plain kernel, streaming consumer); also through
+    four 128x64 tiles of the two-producer-group (2:1) kernel;
   * N at the C-panel limit (256 N 4 bytes just below 2^31);
   * an output of more than 2^32 bytes (M = 2^21, N = 640), with whole tiles
     (plain kernel) and with a partial last tile row (general variant).
@@ -18,7 +18,7 @@ import torch
 import oracle
 from oracle.check import compare_exact, compare_tol
 from paper_2506_11209_amd import inputs
-from tests.gpu_helpers import REL_TOL, log, sample_rows
+from tests.gpu_helpers import REL_TOL, log, sample_rows, whole_then_auto
 
 w = pytest.importorskip("paper_2506_11209_amd.wsgemm")
 
@@ -32,12 +32,16 @@ def run_rows(M, N, K, dist, seed, rows, tile=TILE, stages=STAGES, np_=NP):
     g = w.WsGemm(M, N, K, tile, stages, np_, NC, "bf16")
     try:
         Ad, Bd = A.cuda(), B.cuda()
-        C = torch.empty((M, N), dtype=torch.float32, device="cuda")
-        g(Ad, Bd, C)
-        assert g.sync_status() == w.WS_OK
         info = g.info.as_dict()
-        sub = C[torch.as_tensor(rows, device="cuda")].cpu().numpy()
-        del Ad, Bd, C
+
+        def call():
+            C = torch.empty((M, N), dtype=torch.float32, device="cuda")
+            g(Ad, Bd, C)
+            assert g.sync_status() == w.WS_OK
+            return C[torch.as_tensor(rows, device="cuda")].cpu().numpy()
+
+        sub = whole_then_auto(g, call)
+        del Ad, Bd
     finally:
         g.close()
     ref = oracle.gemm_rows(inputs.bits(A), inputs.bits(B), "bf16", rows)
@@ -54,7 +58,7 @@ def test_k_at_the_a_panel_limit():
 
 
 def test_k_at_the_a_panel_limit_whole_tiles():
-    # one whole 256 x 128 tile: the plain kernel, so the deep-prefetch consumer's
+    # one whole 256 x 128 tile: the plain kernel, so the streaming consumer's
     # asm K loop runs 65535 K-iterations
     M, N, K = 256, 128, (1 << 31) // (2 * 256) - 64
     log("case max K whole tile %dx%dx%d" % (M, N, K))
@@ -66,7 +70,7 @@ def test_k_at_the_a_panel_limit_whole_tiles():
 
 
 def test_k_at_the_a_panel_limit_two_producer_groups():
-    # four whole 128 x 64 tiles of the 2:1 plain kernel (deep-prefetch consumer
+    # four whole 128 x 64 tiles of the 2:1 plain kernel (streaming consumer
     # with 168 registers a wave), 65535 K-iterations each
     M, N, K = 256, 128, (1 << 31) // (2 * 256) - 64
     log("case max K 2:1 128x64x64 %dx%dx%d" % (M, N, K))

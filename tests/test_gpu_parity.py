@@ -122,7 +122,7 @@ def test_delays_keep_results_exact(pdelay, cdelay, load_path):
     from paper_2506_11209_amd import wsgemm as w
     A, B = inputs.make_operands(512, 512, 1024, "bf16", "int4", 9)
     log("case delays p=%d c=%d %s" % (pdelay, cdelay, load_path))
-    g = w.WsGemm(512, 512, 1024, (128, 128, 64), 2, 4, 4, "bf16", load_path)
+    g = w.WsGemm(512, 512, 1024, (128, 128, 64), 2, 4, 4, "bf16", load_path, whole_tiles=True)
     try:
         g.set_debug(0, pdelay, cdelay)
         C = g(A.cuda(), B.cuda())
@@ -137,7 +137,7 @@ def test_watchdog_reports_timeout_then_recovers(load_path):
     from paper_2506_11209_amd import wsgemm as w
     A, B = inputs.make_operands(512, 512, 1024, "bf16", "int4", 10)
     log("case watchdog %s" % load_path)
-    g = w.WsGemm(512, 512, 1024, (128, 128, 64), 2, 4, 4, "bf16", load_path)
+    g = w.WsGemm(512, 512, 1024, (128, 128, 64), 2, 4, 4, "bf16", load_path, whole_tiles=True)
     try:
         Ad, Bd = A.cuda(), B.cuda()
         g.set_debug(1, 20, 0)  # one poll allowed, producers ~160k cycles late
@@ -214,7 +214,8 @@ def test_full_size_workload(name, point, load_path):
         s, _ = w.ws_gemm_create(wl.M, wl.N, wl.K, cfg)
         assert s == w.WS_ERR_LDS_OVERFLOW
         return
-    g = w.WsGemm(wl.M, wl.N, wl.K, (tm, tn, tk), stages, np_, nc, wl.dtype, load_path, split=split)
+    g = w.WsGemm(wl.M, wl.N, wl.K, (tm, tn, tk), stages, np_, nc, wl.dtype, load_path, split=split,
+                 whole_tiles=True)
     try:
         C = torch.full((wl.M, wl.N), float("nan"), dtype=torch.float32, device="cuda")
         g(f.Ad, f.Bd, C)

@@ -6,7 +6,7 @@ import pytest
 import torch
 
 from paper_2506_11209_amd import inputs
-from tests.gpu_helpers import check_full, log
+from tests.gpu_helpers import check_full, log, whole_then_auto
 
 pytestmark = pytest.mark.gpu
 
@@ -25,12 +25,15 @@ def run_ragged(A, B, tile, stages, np_, nc, dtype, load_path="registers"):
     g = w.WsGemm(M, N, K, tile, stages, np_, nc, dtype, load_path)
     try:
         assert g.info.ragged == 1
-        buf = torch.full((M * N + GUARD,), SENTINEL, dtype=torch.float32, device="cuda")
-        C = buf[:M * N].view(M, N)
         Ad, Bd = A.cuda(), B.cuda()  # held until the kernel has finished
-        g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), C.data_ptr(), torch.cuda.current_stream().cuda_stream)
-        assert g.sync_status() == w.WS_OK
-        out = buf.cpu().numpy()
+
+        def call():
+            buf = torch.full((M * N + GUARD,), SENTINEL, dtype=torch.float32, device="cuda")
+            g.run_ptrs(Ad.data_ptr(), Bd.data_ptr(), buf.data_ptr(), torch.cuda.current_stream().cuda_stream)
+            assert g.sync_status() == w.WS_OK
+            return buf.cpu().numpy()
+
+        out = whole_then_auto(g, call)
         return out[:M * N].reshape(M, N), out[M * N:]
     finally:
         g.close()
