@@ -23,9 +23,6 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 OUT = os.path.join(HERE, "ws_deep_loop.inc")
 
-# Configurations of a deep-prefetch block: none (the streaming consumer,
-# gen_stream_loop.py, runs all that had one).
-CONFIGS: list = []
 HEADER_BYTES = 256
 LGKM_MAX = 15
 

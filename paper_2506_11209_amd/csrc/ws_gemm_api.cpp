@@ -270,7 +270,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
   // costs of the whole problem: part_cost units are ns per 64 of K
   const int64_t slabs = (K + 63) / 64;
   const int64_t whole_cost = wsg::tiles_cost(whole.plan.tiles, c.tile_m, c.tile_n, cus) * slabs;
-  int64_t best = whole_cost * 10 / 11;  // what another partition must not exceed
+  int64_t best = whole_cost * wsg::kPartitionGainNum / wsg::kPartitionGainDen;  // what another partition must not exceed
   ws_gemm_config part{}, rest{};
   each_part(c, cus, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
             [&](const ws_gemm_config& k, int64_t cost) {
@@ -458,7 +458,6 @@ struct ws_gemm_handle {
   int64_t M, N, K;
   ws_gemm_config cfg;
   wsg::PlanOut plan;
-  const wsg::KernelEntry* kernel;
   const wsg::KernelEntry* traced;  // instrumented variant (null if none was compiled)
   const wsg::KernelEntry* general; // general twin (partial tiles, epilogue options), or null
   wsg::PlanOut plan_plain, plan_general;  // whole-tile plans of the plain and the general kernel
@@ -567,7 +566,6 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   if (!k) return WS_ERR_UNSUPPORTED;
   const wsg::KernelEntry* general =
       kind == WS_CALIB_NONE ? find_kernel(*cfg, 0, wsg::kModeGemm, 1) : nullptr;
-  const wsg::KernelEntry* run = k;
   const void* launch_fn = k->fn;
   if (kind == WS_CALIB_EMPTY) {
     launch_fn = reinterpret_cast<const void*>(&wsg::ws_empty_kernel<0>);
@@ -577,9 +575,9 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
                      : kind == WS_CALIB_MATH    ? wsg::kModeMath
                      : kind == WS_CALIB_LOAD_AB ? wsg::kModeLoadAB
                                                 : wsg::kModeEpilogue;
-    run = find_kernel(*cfg, 0, mode);
-    if (!run) return WS_ERR_UNSUPPORTED;
-    launch_fn = run->fn;
+    const wsg::KernelEntry* calib = find_kernel(*cfg, 0, mode);
+    if (!calib) return WS_ERR_UNSUPPORTED;
+    launch_fn = calib->fn;
   }
 
   WSG_HIP(hipInit(0));
@@ -632,7 +630,6 @@ ws_status create_handle(int64_t M, int64_t N, int64_t K, const ws_gemm_config* c
   h->K = K;
   h->cfg = *cfg;
   h->plan = p;
-  h->kernel = run;
   h->general = general;
   h->plan_plain = p;
   h->plan_general = pg;

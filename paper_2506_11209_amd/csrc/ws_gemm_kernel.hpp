@@ -512,7 +512,7 @@ struct Cfg {
   static constexpr int A_INSTR = A_BYTES / 1024;     // 1 KiB DMA instructions per A tile
   static constexpr int B_INSTR = B_BYTES / 1024;
   static constexpr int CA = TK / 8;                  // 16-byte chunks per A row
-  static constexpr int NQ = TN / 16;                 // B blocks per block-row
+  static constexpr int NQ = TN / 16;                 // 16-column halves of B blocks per block-row
   static_assert(NC == 1 || NC == 4 || NC == 8, "consumer waves must be 1, 4 or 8");
   static_assert(SPLIT == 1 || SPLIT == 2, "split must be 1:1 or 2:1");
   // producer waves: one group of NC (1:1) or two of NC (2:1); with NC = 4 also

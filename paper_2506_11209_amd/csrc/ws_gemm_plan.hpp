@@ -273,7 +273,7 @@ inline int64_t tiles_cost(int64_t tiles, int tm, int tn, int num_cus) {
 // us; 2048x2048x4096 with 256x256x64 tiles (64 tiles) 80 -> 39 us as 128x128
 // parts; 256^3 with 64x64x32 tiles of one consumer wave 7.2 -> 4.9 us as 32x32
 // parts.
-inline bool partition_pays(int64_t cost, int64_t whole) { return cost * 11 <= whole * 10; }
+constexpr int kPartitionGainNum = 10, kPartitionGainDen = 11;
 
 // What a second launch on the stream adds (ns): the first one's drain and the
 // second one's start.

@@ -78,8 +78,9 @@ class Lane:
         r = self.wm * c.wm + (lane & 31)
         self.a_off0 = r * c.tk * 2 + (((lane >> 5) ^ swz_a(c.tk, r)) << 4)
         g = lane >> 4
-        self.b_off = (c.a_bytes + ((2 * (g >> 1)) * c.nq + (self.wn * c.wn) // 16 + (g & 1)) * 128 +
-                      8 * (lane & 15))
+        j = lane & 15
+        self.in_block = (j >> 2) * 64 + (g & 1) * 32 + (j & 3) * 8  # its 8 bytes of a 4 x 32 block (64 bytes a row)
+        self.b_off = c.a_bytes + ((2 * (g >> 1)) * (c.tn // 32) + (self.wn * c.wn) // 32) * 256 + self.in_block
 
     def decode_a(self, within):
         """(kss, mb) of an A read at byte `within` of a slot, or a message."""
@@ -104,16 +105,16 @@ class Lane:
         boff = within - c.a_bytes
         if not 0 <= boff < c.tk * c.tn * 2:
             return "B read outside the B tile (byte %d)" % within
-        block, byte = boff // 128, boff % 128
-        if byte != 8 * (self.lane & 15):
+        block, byte = boff // 256, boff % 256
+        if byte != self.in_block:
             return "B read at byte %d of a block, not lane %d's" % (byte, self.lane)
-        kq, nq = block // c.nq, block % c.nq
+        kq, nd = block // (c.tn // 32), block % (c.tn // 32)
         g = self.lane >> 4
         rem = kq % 4 - 2 * (g >> 1)
-        nrel = nq - (self.wn * c.wn) // 16 - (g & 1)
-        if rem not in (0, 1) or nrel % 2 or not 0 <= nrel // 2 < c.bn:
-            return "B read of block (%d, %d), not lane %d's" % (kq, nq, self.lane)
-        return (kq // 4, nrel // 2, rem)
+        nb = nd - (self.wn * c.wn) // 32
+        if rem not in (0, 1) or not 0 <= nb < c.bn:
+            return "B read of block (%d, %d), not lane %d's" % (kq, nd, self.lane)
+        return (kq // 4, nb, rem)
 
 
 class Sim:
@@ -386,6 +387,10 @@ def test_roll_block_reads_waits_and_releases(key, S, polls, P):
                 assert lines[i + 1] == "s_waitcnt lgkmcnt(0)"
     else:
         assert not sim.stores and not any(l.startswith("s_memtime") for l in lines)
+
+
+def test_committed_file_is_what_the_generator_writes():
+    assert gen.main(["--check"]) == 0
 
 
 def test_generator_covers_the_dispatched_configurations():
