@@ -86,15 +86,21 @@ class Bad(Exception):
 
 
 class Sim:
-    def __init__(self, c, S, polls, P):
+    """polls: looks that find a slot's counter short.  dly: the consumer delay
+    hook.  lim: polls before a wait gives up.  stuck: a K-iteration whose slot never
+    fills.  abort_at: the K-iteration whose wait finds the workgroup's abort flag up."""
+
+    def __init__(self, c, S, polls, P, dly=0, lim=1000, stuck=None, abort_at=None):
         self.c, self.S, self.polls, self.P = c, S, polls, P
+        self.stuck, self.abort_at = stuck, abort_at
+        self.sleeps = 0
         waves = (0, 1, 2, 3) if c.nc == 4 else (0,)
         self.lanes = [Lane(c, w, l) for w in waves for l in (0, 5, 17, 38, 63)]
         self.want = [({l.a_byte(k, m): (k, m) for k in range(c.ks) for m in range(c.bm)},
                       {l.b_byte(k, n, h): (k, n, h) for k in range(c.ks) for n in range(c.bn) for h in (0, 1)})
                      for l in self.lanes]
         self.s = dict(rb=RING, fa=FULL, rt=c.np, ea=EMPTY, ring=RING, rend=RING + P * c.stage, fullb=FULL,
-                      fend=FULL + 4 * P, emptyb=EMPTY, eend=EMPTY + 4 * P, abortb=ABORT, S=S, lim=1000, dly=0)
+                      fend=FULL + 4 * P, emptyb=EMPTY, eend=EMPTY + 4 * P, abortb=ABORT, S=S, lim=lim, dly=dly)
         self.v = {"boff": [l.b_byte(0, 0, 0) for l in self.lanes]}
         for k in range(c.ks):
             self.v["ao%d" % k] = [l.a_byte(k, 0) for l in self.lanes]
@@ -184,6 +190,7 @@ class Sim:
             args = [a.strip() for a in l[len(op):].split(",")]
             i += 1
             if re.fullmatch(r"\d+:", l) or op in ("s_nop", "s_sleep"):
+                self.sleeps += l == "s_sleep 127"
                 continue
             if op.startswith("s_cbranch") or op == "s_branch":
                 assert op in ("s_branch", "s_cbranch_scc1")
@@ -199,7 +206,7 @@ class Sim:
             elif op == "ds_read_b32":
                 at = self.vec(args[1])[0]
                 if at == ABORT:
-                    x = 0
+                    x = int(max(self.full) + 1 == self.abort_at)
                 else:
                     u = max(self.full) + 1
                     if at != FULL + 4 * (u % self.P):
@@ -207,7 +214,8 @@ class Sim:
                     if u - self.P >= self.released and self.looks.get(u, 0) > 0:
                         raise Bad("K-iteration %d waited for while its slot is held" % u)
                     looks = self.looks[u] = self.looks.get(u, 0) + 1
-                    x = c.np * (u // self.P + 1) - (1 if looks <= self.polls else 0)
+                    short = looks <= (self.polls if u != self.stuck else looks)
+                    x = c.np * (u // self.P + 1) - (1 if short else 0)
                 self.pending.append(([args[0]], x, None))
             elif op == "ds_add_u32":
                 if self.exec != 1 or self.v["one"][0] != 1 or self.vec(args[0])[0] != EMPTY + 4 * (self.released % self.P):
@@ -273,6 +281,37 @@ def test_block_on_every_path(key):
         for polls in (0, 1, 3):
             for P in (2, 3, 5):
                 Sim(c, S, polls, P).run(BLOCKS[key])
+
+
+@pytest.mark.parametrize("key", sorted(k for k in BLOCKS if k[5]), ids=str)
+def test_delay_hook(key):
+    """Every K-iteration that the block enters without draining sleeps dly times;
+    the delay changes nothing else."""
+    c = gen.Cfg(*key[:5])
+    for S in range(c.m, c.m + 4):
+        for polls in (0, 1):
+            sim = Sim(c, S, polls, 3, dly=3)
+            sim.run(BLOCKS[key])
+            assert sim.sleeps == 2 * 3 * (S - 1), (S, polls)
+        drained = Sim(c, S, 3, 3, dly=3)
+        drained.run(BLOCKS[key])
+        assert drained.sleeps == (0 if c.drain else 2 * 3 * (S - 1))
+
+
+@pytest.mark.parametrize("key", sorted(k for k in BLOCKS if k[5]), ids=str)
+def test_every_wait_gives_up(key):
+    """A slot that never fills, or an abort raised by another wave, ends the block
+    at that K-iteration's wait with status 2 or 1, nothing in flight, every lane
+    enabled and no slot released that is still read."""
+    c = gen.Cfg(*key[:5])
+    for S in range(c.m + 1, c.m + 4):
+        for P in (2, 3, 5):
+            for u in range(1, S):
+                for st, kw in ((2, dict(lim=4)), (1, dict(abort_at=u))):
+                    sim = Sim(c, S, 0, P, stuck=u, **kw)
+                    sim.tile(BLOCKS[key])
+                    assert sim.s["st"] == st and not sim.pending and sim.exec == -1
+                    assert max(sim.full) == u - 1 and sim.released <= u
 
 
 def test_committed_file_is_what_the_generator_writes():
