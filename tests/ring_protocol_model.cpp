@@ -29,7 +29,15 @@
 // K-iteration q + 1 is full before it releases q.  The least a blocked
 // producer may signal is every pending K-iteration up to q - P + 1 (the
 // consumers need it to release q - P); PLANT_SHORT_DRAIN stops one short of
-// that.
+// that.  Where the ring has two or three slots every second consumer drains
+// instead of waiting there, as the kernels' streaming consumer does: finding
+// q + 1 not full, it releases q and only then waits.
+//
+// A seventh argument GROUPS splits the producers into that many groups: group
+// g writes the K-iterations q with q % GROUPS == g, all NP / GROUPS of its
+// threads, and each adds GROUPS to full[], so that a slot's use still counts
+// NP.  Their slots are GROUPS apart, so at odd ring depths two groups write the
+// same slot in turn.
 //
 // Planted mistakes, selected with -D for the tests that must catch them:
 //   PLANT_EARLY_RELEASE  consumers release the slot before reading it
@@ -37,6 +45,9 @@
 //   PLANT_DROP_SIGNAL    producer 0 skips its signal of K-iteration T/2
 //   PLANT_SHORT_DRAIN    (with LAG) a blocked producer signals pending
 //                        K-iterations only up to q - P
+//   PLANT_GROUP_COUNT    (with GROUPS) a producer signals one, not GROUPS
+//   PLANT_GROUP_SHARE    (with GROUPS) consumers take a slot as full at the
+//                        count of one producer group fewer
 //   PLANT_PEEK_WRONG_SLOT the counter read with a signal is the signalled
 //                        slot's, not the next one's
 #include <atomic>
@@ -56,6 +67,7 @@ constexpr int kChunks = 8;  // words each producer writes per slot use
 struct Ring {
   uint32_t P, NP, NC, T;
   int lag = -1;  // < 0: signal each K-iteration as soon as it is written
+  uint32_t groups = 1;
   long long limit_ms;
   std::vector<std::atomic<uint32_t>> full, empty;
   std::vector<uint64_t> data;  // [P][NP][kChunks], plain memory
@@ -96,13 +108,22 @@ bool wait_for(Ring& r, std::atomic<uint32_t>& ctr, uint32_t target) {
   return true;
 }
 
+constexpr uint32_t signal_count(const Ring& r) {
+#ifdef PLANT_GROUP_COUNT
+  return (void)r, 1;
+#else
+  return r.groups;
+#endif
+}
+
 // The register-staged producer: it walks the slots incrementally and, with
 // each signal, reads the empty[] counter of the slot it writes next; it
 // waits on that slot only when the value read does not already reach the
 // target (the counters are monotonic).
 void producer(Ring& r, uint32_t p) {
-  uint32_t w_slot = 0, w_need = 0, seen = 0;
-  for (uint32_t q = 0; q < r.T; ++q) {
+  const uint32_t grp = p % r.groups;
+  uint32_t w_slot = grp, w_need = 0, seen = 0;
+  for (uint32_t q = grp; q < r.T; q += r.groups) {
     const uint32_t slot = w_slot;
     if (slot != wsg::ring_slot(q, r.P) || w_need != wsg::ring_empty_target(q, r.P, r.NC)) {
       r.mismatches.fetch_add(1);  // the incremental walk disagrees with the closed forms
@@ -111,14 +132,15 @@ void producer(Ring& r, uint32_t p) {
     if ((int32_t)(seen - w_need) < 0 && !wait_for(r, r.empty[slot], w_need)) return;
     uint64_t* d = r.share(slot, p);
     for (int c = 0; c < kChunks; ++c) d[c] = tag(q, p, c);
-    if (++w_slot == r.P) {
-      w_slot = 0;
+    w_slot += r.groups;
+    if (w_slot >= r.P) {
+      w_slot -= r.P;
       w_need += r.NC;
     }
 #ifdef PLANT_DROP_SIGNAL
     if (!(p == 0 && q == r.T / 2))  // only the signal goes missing; the peek below still runs
 #endif
-      r.full[slot].fetch_add(1, std::memory_order_release);
+      r.full[slot].fetch_add(signal_count(r), std::memory_order_release);
 #ifdef PLANT_PEEK_WRONG_SLOT
     seen = r.empty[slot].load(std::memory_order_acquire);
 #else
@@ -131,12 +153,13 @@ void producer(Ring& r, uint32_t p) {
 // wait keeps the consumers' one-K-iteration look-ahead satisfied.
 void producer_deferred(Ring& r, uint32_t p) {
   const uint32_t lag = (uint32_t)r.lag;
-  uint32_t q_sig = 0;
+  const uint32_t grp = p % r.groups;
+  uint32_t q_sig = grp;
   auto publish = [&]() {
-    r.full[wsg::ring_slot(q_sig, r.P)].fetch_add(1, std::memory_order_release);
-    ++q_sig;
+    r.full[wsg::ring_slot(q_sig, r.P)].fetch_add(signal_count(r), std::memory_order_release);
+    q_sig += r.groups;
   };
-  for (uint32_t q = 0; q < r.T; ++q) {
+  for (uint32_t q = grp; q < r.T; q += r.groups) {
     const uint32_t slot = wsg::ring_slot(q, r.P);
     if (wsg::ring_use(q, r.P) > 0) {
       const uint32_t need = wsg::ring_empty_target(q, r.P, r.NC);
@@ -151,28 +174,35 @@ void producer_deferred(Ring& r, uint32_t p) {
     }
     uint64_t* d = r.share(slot, p);
     for (int c = 0; c < kChunks; ++c) d[c] = tag(q, p, c);
-    if (q + 1 - q_sig > lag) publish();
+    if ((q - q_sig) / r.groups + 1 > lag) publish();
   }
   while (q_sig < r.T) publish();
 }
 
-void consume(Ring& r, uint32_t q, uint32_t slot, uint32_t target) {
+void consume(Ring& r, uint32_t q, uint32_t slot, uint32_t target, bool drains) {
 #ifdef PLANT_EARLY_READ
   target -= 1;
+#endif
+#ifdef PLANT_GROUP_SHARE
+  target -= r.groups;
 #endif
   if (!wait_for(r, r.full[slot], target)) return;
 #ifdef PLANT_EARLY_RELEASE
   r.empty[slot].fetch_add(1, std::memory_order_release);
 #endif
-  for (uint32_t p = 0; p < r.NP; ++p) {
+  for (uint32_t p = q % r.groups; p < r.NP; p += r.groups) {
     const uint64_t* d = r.share(slot, p);
     for (int c = 0; c < kChunks; ++c)
       if (d[c] != tag(q, p, c)) r.mismatches.fetch_add(1);
   }
-  // the kernels' consumers see K-iteration q + 1 full before releasing q
-  if (r.lag >= 0 && q + 1 < r.T &&
-      !wait_for(r, r.full[wsg::ring_slot(q + 1, r.P)], wsg::ring_full_target(q + 1, r.P, r.NP)))
-    return;
+  // the kernels' consumers see K-iteration q + 1 full before releasing q, or
+  // find it short and release q first (the next call then waits)
+  if (r.lag >= 0 && q + 1 < r.T) {
+    std::atomic<uint32_t>& next = r.full[wsg::ring_slot(q + 1, r.P)];
+    const uint32_t want = wsg::ring_full_target(q + 1, r.P, r.NP);
+    const bool is_short = (int32_t)(next.load(std::memory_order_acquire) - want) < 0;
+    if (!(drains && r.P <= 3 && is_short) && !wait_for(r, next, want)) return;
+  }
 #ifndef PLANT_EARLY_RELEASE
   r.empty[slot].fetch_add(1, std::memory_order_release);
 #endif
@@ -180,7 +210,7 @@ void consume(Ring& r, uint32_t q, uint32_t slot, uint32_t target) {
 
 void consumer_closed_form(Ring& r) {
   for (uint32_t q = 0; q < r.T && !r.abort.load(std::memory_order_relaxed); ++q)
-    consume(r, q, wsg::ring_slot(q, r.P), wsg::ring_full_target(q, r.P, r.NP));
+    consume(r, q, wsg::ring_slot(q, r.P), wsg::ring_full_target(q, r.P, r.NP), false);
 }
 
 void consumer_incremental(Ring& r) {
@@ -190,7 +220,7 @@ void consumer_incremental(Ring& r) {
       r.mismatches.fetch_add(1);  // the two walks disagree
       return;
     }
-    consume(r, q, slot, target);
+    consume(r, q, slot, target, true);
     wsg::ring_advance(slot, target, r.P, r.NP);
   }
 }
@@ -198,25 +228,28 @@ void consumer_incremental(Ring& r) {
 }  // namespace
 
 int main(int argc, char** argv) {
-  if (argc != 6 && argc != 7) {
-    std::fprintf(stderr, "usage: %s P NP NC T WAIT_LIMIT_MS [LAG]\n", argv[0]);
+  if (argc < 6 || argc > 8) {
+    std::fprintf(stderr, "usage: %s P NP NC T WAIT_LIMIT_MS [LAG [GROUPS]]\n", argv[0]);
     return 3;
   }
   const long P = std::atol(argv[1]), NP = std::atol(argv[2]), NC = std::atol(argv[3]);
   const long T = std::atol(argv[4]);
   const long long limit = std::atoll(argv[5]);
   if (P < 1 || P > 64 || NP < 1 || NP > 64 || NC < 1 || NC > 64 || T < 1 || limit < 1) return 3;
-  const long lag = argc == 7 ? std::atol(argv[6]) : -1;
+  const long lag = argc >= 7 ? std::atol(argv[6]) : -1;
+  const long groups = argc == 8 ? std::atol(argv[7]) : 1;
+  if (groups < 1 || groups > P || NP % groups) return 3;  // a lap takes a group at most once past the end
   // a consumer that looks one K-iteration ahead needs two slots at least
   if (lag < -1 || lag > 64 || (lag >= 0 && P < 2)) return 3;
   Ring r((uint32_t)P, (uint32_t)NP, (uint32_t)NC, (uint32_t)T, limit);
   r.lag = (int)lag;
+  r.groups = (uint32_t)groups;
   std::vector<std::thread> th;
   for (uint32_t p = 0; p < r.NP; ++p) th.emplace_back(lag >= 0 ? producer_deferred : producer, std::ref(r), p);
   for (uint32_t c = 0; c < r.NC; ++c)
     th.emplace_back((c % 2) ? consumer_incremental : consumer_closed_form, std::ref(r));
   for (auto& t : th) t.join();
-  std::printf("P=%ld NP=%ld NC=%ld T=%ld lag=%ld timeouts=%d mismatches=%d\n", P, NP, NC, T, lag,
+  std::printf("P=%ld NP=%ld NC=%ld T=%ld lag=%ld groups=%ld timeouts=%d mismatches=%d\n", P, NP, NC, T, lag, groups,
               r.timeouts.load(), r.mismatches.load());
   if (r.timeouts.load()) return 2;
   if (r.mismatches.load()) return 1;
