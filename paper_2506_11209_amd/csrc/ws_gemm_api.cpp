@@ -757,7 +757,7 @@ ws_status ws_gemm_clock(ws_gemm_t h, hipStream_t stream, uint64_t* shader_cycles
 ws_status ws_gemm_query(ws_gemm_t h, ws_gemm_plan_info* out) {
   if (!h || !out) return WS_ERR_INVALID_ARG;
   to_info(h->plan, out);
-  out->general = (h->use_general || h->plan.ragged) ? 1 : 0;
+  out->general = (h->plan.ragged || (h->use_general && h->plan.grid > 0)) ? 1 : 0;  // empty: no GEMM kernel
   return WS_OK;
 }
 

@@ -71,6 +71,7 @@ def test_k_zero_epilogue(alpha, beta, out):
     g = handle(M, N, 0, CONFIGS[0])
     try:
         g.set_epilogue(alpha, beta, out)
+        assert g.info.general == 0 and g.launches() == []  # no GEMM kernel runs, general or not
         C_in = inputs.make_output(M, N, out, "int4", 17)
         buf = torch.full((M * N + GUARD,), SENTINEL, dtype=TORCH_OUT[out])
         buf[:M * N] = C_in.reshape(-1)
