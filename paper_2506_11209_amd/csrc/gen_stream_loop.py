@@ -47,6 +47,11 @@ rings do not win back.  Waiting -> draining, 64x64x64: two slots
 241), 64x4096x4096 23.3 -> 21.3 us; 128x128x64 2048x2048x32768 three slots
 286 -> 279 us, four slots 264 -> 265 us and the general kernel 277 -> 302 us.
 
+At KS = 2 four sets read more than a slot ahead: the check of K-iteration u + 2
+stands right behind the release of u, whose slot it needs in a ring of two, with
+all of u + 1 still to multiply.  There a second block with two sets (tile_short)
+checks u + 1 at the end of u.
+
 The loop body is U = lcm(KS, F) k-steps, m = U / KS K-iterations.  A tile
 whose S is not a multiple of m enters its first body at the k-step that makes
 the rest whole (one prologue per remainder).  Tiles with S < m take the
@@ -91,11 +96,17 @@ CONFIGS = {
 
 
 class Cfg:
-    def __init__(self, tm, tn, tk, nc, np):
+    """A configuration's block; short: the one for rings of two slots."""
+
+    def __init__(self, tm, tn, tk, nc, np, short=False):
         assert nc in (1, 4) and tk in (32, 64)
         self.tm, self.tn, self.tk, self.nc, self.np = tm, tn, tk, nc, np
         self.f, self.vgprs = CONFIGS[(tm, tn, tk, nc, np)]
         self.ks = tk // 16
+        self.has_short = self.f - 1 > self.ks
+        if short:
+            assert self.has_short
+            self.f = 2
         self.wm, self.wn = (tm // 2, tn // 2) if nc == 4 else (tm, tn)
         self.bm, self.bn = self.wm // 32, self.wn // 32
         self.nd = tn // 32                            # B blocks (256 bytes) per block row
@@ -474,7 +485,7 @@ def gen_block(c: Cfg, bf16: bool) -> list[str]:
     return E.lines
 
 
-def gen_struct(c: Cfg, bf16: bool) -> str:
+def gen_tile(c: Cfg, bf16: bool, name: str) -> str:
     # Every in/out operand is early-clobber: the block writes it long before it
     # last reads its inputs, and the cursor starts out equal to some of them
     # (slot and ring, full and full0, empty and empty0), which would else let
@@ -484,12 +495,7 @@ def gen_struct(c: Cfg, bf16: bool) -> str:
     ao = ", ".join('[ao%d] "v"(a_off[%d])' % (k, k) for k in range(c.ks if c.f > 1 else 1))
     clobbers = ", ".join('"v%d"' % r for r in range(c.frag_base, c.vgprs))
     body = "\n".join('        "%s\\n\\t"' % l for l in lines)
-    return """template <>
-struct StreamLoop<%(tm)d, %(tn)d, %(tk)d, %(nc)d, %(np)d, %(bf16)s> {
-  static constexpr bool kAvailable = true;
-  static constexpr int kMinIters = %(m)d;  // fewest K-iterations of a tile
-  static constexpr int kVgprs = %(vgprs)d;
-  static __device__ __forceinline__ uint32_t tile(f32x16_t (&c)[%(bm)d][%(bn)d], const uint32_t (&a_off)[%(ks)d],
+    return """  static __device__ __forceinline__ uint32_t %(name)s(f32x16_t (&c)[%(bm)d][%(bn)d], const uint32_t (&a_off)[%(ks)d],
                                                   uint32_t boff, RingCursor& r, uint32_t S, int32_t lim,
                                                   int32_t dly) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -509,9 +515,22 @@ struct StreamLoop<%(tm)d, %(tn)d, %(tk)d, %(nc)d, %(np)d, %(bf16)s> {
     return 0;
 #endif
   }
-};
-""" % dict(tm=c.tm, tn=c.tn, tk=c.tk, nc=c.nc, np=c.np, bf16="true" if bf16 else "false", bm=c.bm, bn=c.bn,
-           ks=c.ks, m=c.m, vgprs=c.vgprs, body=body, acc=acc_ops, ao=ao, clobbers=clobbers)
+""" % dict(name=name, bm=c.bm, bn=c.bn, ks=c.ks, body=body, acc=acc_ops, ao=ao, clobbers=clobbers)
+
+
+def gen_struct(t, bf16: bool) -> str:
+    c = Cfg(*t)
+    blocks = [gen_tile(c, bf16, "tile")]
+    if c.has_short:
+        blocks.append(gen_tile(Cfg(*t, short=True), bf16, "tile_short"))
+    return """template <>
+struct StreamLoop<%d, %d, %d, %d, %d, %s> {
+  static constexpr bool kAvailable = true;
+  static constexpr int kMinIters = %d;  // fewest K-iterations of a tile
+  static constexpr int kVgprs = %d;
+  static constexpr bool kShort = %s;  // tile_short is the block for two slots
+%s};
+""" % (*t, "true" if bf16 else "false", c.m, c.vgprs, "true" if c.has_short else "false", "\n".join(blocks))
 
 
 def generate() -> str:
@@ -524,11 +543,12 @@ def generate() -> str:
              "  static constexpr bool kAvailable = false;",
              "  static constexpr int kMinIters = 1;",
              "  static constexpr int kVgprs = 0;",
+             "  static constexpr bool kShort = false;",
              "};",
              ""]
     for t in CONFIGS:
         for bf16 in (True, False):
-            parts.append(gen_struct(Cfg(*t), bf16))
+            parts.append(gen_struct(t, bf16))
     return "\n".join(parts)
 
 

@@ -1515,7 +1515,12 @@ __device__ __forceinline__ void consumer_stream(const KernelArgs& args, WSG_LDS 
   const uint32_t b_off = G::A_BYTES + b_read_off<TN>(lane, wn * G::WN);
 
   const uint32_t S = (uint32_t)args.iters;
-  if (Loop::kMinIters > 1 && S < (uint32_t)Loop::kMinIters) {
+  // T_K = 32 in a ring of two slots takes the block with two fragment sets
+  // (see gen_stream_loop.py).  Four sets -> two: 128x64x32 at 2048x2048x4096
+  // 93.0 -> 67.0 us, 256x128x32 (2:1, eight waves) at 2048x4096x4096 117.7 ->
+  // 80.5 us, 32x32x32 at 256x256x4096 57.9 -> 34.0 us; three slots keep four.
+  const bool short_ring = Loop::kShort && args.stages < 3;  // wave-uniform
+  if (Loop::kMinIters > 1 && S < (uint32_t)Loop::kMinIters && !short_ring) {
     consumer<TM, TN, TK, NC, NPW, SPLIT, BF16, false, MODE, GENERAL>(args, smem, cw, lane);
     return;
   }
@@ -1544,7 +1549,19 @@ __device__ __forceinline__ void consumer_stream(const KernelArgs& args, WSG_LDS 
       for (int nb = 0; nb < BN; ++nb) acc[mb][nb] = f32x16_t{};
     if (!wait_counter((WSG_LDS uint32_t*)(uintptr_t)rc.full, rc.target, abort_flag, args.spin_limit, args.err))
       return;
-    const uint32_t st = Loop::tile(acc, a_off, b_off, rc, S, args.spin_limit, args.consumer_delay);
+    uint32_t st;
+    if constexpr (Loop::kShort) {
+      st = short_ring ? Loop::tile_short(acc, a_off, b_off, rc, S, args.spin_limit, args.consumer_delay)
+                      : Loop::tile(acc, a_off, b_off, rc, S, args.spin_limit, args.consumer_delay);
+      // the two blocks' scalar results meet here; the compiler does not see that they are uniform
+      rc.slot = __builtin_amdgcn_readfirstlane(rc.slot);
+      rc.full = __builtin_amdgcn_readfirstlane(rc.full);
+      rc.target = __builtin_amdgcn_readfirstlane(rc.target);
+      rc.empty = __builtin_amdgcn_readfirstlane(rc.empty);
+      st = __builtin_amdgcn_readfirstlane(st);
+    } else {
+      st = Loop::tile(acc, a_off, b_off, rc, S, args.spin_limit, args.consumer_delay);
+    }
     if (st != 0) {
       if (st == 2) report_timeout(abort_flag, args.err);
       return;

@@ -40,8 +40,14 @@ def blocks():
     out = {}
     for m in re.finditer(r"struct StreamLoop<(\d+), (\d+), (\d+), (\d+), (\d+), (true|false)> \{(.*?)\n\};", text, re.S):
         key = tuple(int(x) for x in m.groups()[:5]) + (m.group(6) == "true",)
-        out[key] = [l.strip() for l in re.findall(r'^\s*"(.*)\\n\\t"$', m.group(7), re.M)]
+        for fn in re.finditer(r"uint32_t (tile|tile_short)\((.*?)return st;", m.group(7), re.S):
+            lines = re.findall(r'^\s*"(.*)\\n\\t"$', fn.group(2), re.M)
+            out[key + (fn.group(1) == "tile_short",)] = [l.strip() for l in lines]
     return out
+
+
+def cfg_of(key):
+    return gen.Cfg(*key[:5], short=key[6])
 
 
 BLOCKS = blocks()
@@ -94,6 +100,7 @@ class Sim:
         self.c, self.S, self.polls, self.P = c, S, polls, P
         self.stuck, self.abort_at = stuck, abort_at
         self.sleeps = 0
+        self.ahead = 0           # most K-iterations still to multiply at the check of the next one's slot
         waves = (0, 1, 2, 3) if c.nc == 4 else (0,)
         self.lanes = [Lane(c, w, l) for w in waves for l in (0, 5, 17, 38, 63)]
         self.want = [({l.a_byte(k, m): (k, m) for k in range(c.ks) for m in range(c.bm)},
@@ -230,6 +237,8 @@ class Sim:
                 self.ready([args[1]])
                 s[name] = self.data[args[1]]
                 u = max(self.full) + 1
+                if args[1] == "%[vp]":
+                    self.ahead = max(self.ahead, u - self.mfmas / (c.ks * c.bm * c.bn))
                 if args[1] == "%[vp]" and s[name] >= c.np * (u // self.P + 1) and s[name] == s["rt"]:
                     self.full.add(u)
             elif op == "v_mov_b32":
@@ -276,7 +285,7 @@ class Sim:
 
 @pytest.mark.parametrize("key", sorted(BLOCKS), ids=str)
 def test_block_on_every_path(key):
-    c = gen.Cfg(*key[:5])
+    c = cfg_of(key)
     for S in range(c.m, c.m + 6):
         for polls in (0, 1, 3):
             for P in (2, 3, 5):
@@ -287,7 +296,7 @@ def test_block_on_every_path(key):
 def test_delay_hook(key):
     """Every K-iteration that the block enters without draining sleeps dly times;
     the delay changes nothing else."""
-    c = gen.Cfg(*key[:5])
+    c = cfg_of(key)
     for S in range(c.m, c.m + 4):
         for polls in (0, 1):
             sim = Sim(c, S, polls, 3, dly=3)
@@ -299,11 +308,23 @@ def test_delay_hook(key):
 
 
 @pytest.mark.parametrize("key", sorted(k for k in BLOCKS if k[5]), ids=str)
+def test_two_slots_wait_with_less_than_a_k_iteration_in_hand(key):
+    """In a ring of two slots the slot that a K-iteration waits for is filled while
+    the one before it multiplies: a block that waits with a whole K-iteration read
+    and none of it multiplied would load and multiply in turn."""
+    c = cfg_of(key)
+    sim = Sim(c, c.m + 4, 0, 2)
+    sim.run(BLOCKS[key])
+    two_slots = key[6] or not c.has_short
+    assert (sim.ahead < 1) == two_slots, sim.ahead
+
+
+@pytest.mark.parametrize("key", sorted(k for k in BLOCKS if k[5]), ids=str)
 def test_every_wait_gives_up(key):
     """A slot that never fills, or an abort raised by another wave, ends the block
     at that K-iteration's wait with status 2 or 1, nothing in flight, every lane
     enabled and no slot released that is still read."""
-    c = gen.Cfg(*key[:5])
+    c = cfg_of(key)
     for S in range(c.m + 1, c.m + 4):
         for P in (2, 3, 5):
             for u in range(1, S):
@@ -316,7 +337,8 @@ def test_every_wait_gives_up(key):
 
 def test_committed_file_is_what_the_generator_writes():
     assert gen.main(["--check"]) == 0
-    assert set(BLOCKS) == {k + (b,) for k in gen.CONFIGS for b in (True, False)}
+    assert set(BLOCKS) == {k + (b, short) for k in gen.CONFIGS for b in (True, False)
+                           for short in ((False, True) if gen.Cfg(*k).has_short else (False,))}
 
 
 def shared_register_hazards(text):
@@ -346,7 +368,7 @@ def test_operands_written_early_share_no_register_with_an_input():
 
 @pytest.mark.parametrize("key", sorted(k for k in BLOCKS if k[5]), ids=str)
 def test_planted_mistakes_are_caught(key):
-    lines, c = BLOCKS[key], gen.Cfg(*key[:5])
+    lines, c = BLOCKS[key], cfg_of(key)
 
     def caught(bad):
         for S in range(c.m, c.m + 4):
