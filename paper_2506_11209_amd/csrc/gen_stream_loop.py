@@ -76,7 +76,10 @@ from gen_deep_loop import Emitter, HEADER_BYTES, LGKM_MAX  # noqa: E402
 OUT = os.path.join(HERE, "ws_stream_loop.inc")
 
 # (TM, TN, TK, NC, NP): (fragment sets F, registers a wave).  Four consumer
-# waves in a 2 x 2 grid, or one.
+# waves in a 2 x 2 grid, or one.  The smallest tiles have the fewest registers:
+# what hides their latency is the number of workgroups that share a CU (168 and
+# 128 -> 80 registers: 32x32x32 2:1 at 1344x864x2944, two slots, 112.5 -> 41.2 us;
+# 64x64x32 2:1 by four waves at 2944x960x2784 83.3 -> 50.3 us).
 CONFIGS = {
     (256, 128, 64, 4, 4): (4, 256), (128, 256, 64, 4, 4): (4, 256), (128, 128, 64, 4, 4): (4, 256),
     (64, 128, 64, 4, 4): (4, 256), (128, 64, 64, 4, 4): (4, 256), (64, 64, 64, 4, 4): (4, 128),
@@ -85,10 +88,10 @@ CONFIGS = {
     (64, 64, 64, 4, 8): (4, 168),
     (128, 128, 32, 4, 8): (4, 168), (128, 64, 32, 4, 8): (4, 168), (64, 128, 32, 4, 8): (4, 168),
     (64, 64, 32, 4, 8): (4, 168),
-    (64, 128, 32, 4, 4): (4, 128), (128, 64, 32, 4, 4): (4, 128), (64, 64, 32, 4, 4): (4, 128),
-    (32, 32, 32, 1, 1): (4, 168), (32, 32, 64, 1, 1): (4, 168), (64, 64, 32, 1, 1): (4, 256),
+    (64, 128, 32, 4, 4): (4, 128), (128, 64, 32, 4, 4): (4, 128), (64, 64, 32, 4, 4): (4, 80),
+    (32, 32, 32, 1, 1): (4, 128), (32, 32, 64, 1, 1): (4, 168), (64, 64, 32, 1, 1): (4, 256),
     (64, 64, 64, 1, 1): (4, 256),
-    (32, 32, 32, 1, 2): (4, 168), (32, 32, 64, 1, 2): (4, 168), (64, 64, 32, 1, 2): (4, 256),
+    (32, 32, 32, 1, 2): (4, 80), (32, 32, 64, 1, 2): (4, 128), (64, 64, 32, 1, 2): (4, 256),
     (64, 64, 64, 1, 2): (4, 256),
     (128, 256, 32, 4, 8): (1, 168), (256, 128, 32, 4, 8): (1, 168),
     (128, 256, 64, 4, 8): (1, 168), (256, 128, 64, 4, 8): (1, 168),

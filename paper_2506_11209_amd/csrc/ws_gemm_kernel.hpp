@@ -995,8 +995,11 @@ __device__ __forceinline__ void producer_loop_reg(const KernelArgs& args, WSG_LD
   // VGPRs for staged tiles: what the consumers' allocation leaves (256 a wave
   // with eight waves, 168 with twelve; the 128 x 128 x 32 kernel held to 128
   // registers stages its cap of six K-iterations in 96)
-  constexpr bool LEAN = StreamLoop<TM, TN, TK, NC, NPW, BF16>::kVgprs == 128;
-  constexpr int STAGE_VGPRS = LEAN ? (GENERAL ? 64 : 96) : (G::NW <= 8) ? 152 : (NC == 8 ? 128 : 96);
+  constexpr int REGS = StreamLoop<TM, TN, TK, NC, NPW, BF16>::kVgprs;
+  constexpr int STAGE_VGPRS = REGS == 80    ? (GENERAL ? 32 : 48)
+                              : REGS == 128 ? (GENERAL && NC == 4 ? 64 : 96)
+                              : G::NW <= 8  ? 152
+                                            : (NC == 8 ? 128 : 96);
   constexpr int L0 = STAGE_VGPRS / (4 * LOADS);
   constexpr int L1 = (63 / LOADS) < L0 ? (63 / LOADS) : L0;
   constexpr int LCAP = 6 / GROUPS;
@@ -1501,7 +1504,7 @@ __device__ __forceinline__ void consumer_stream(const KernelArgs& args, WSG_LDS 
   using Loop = StreamLoop<TM, TN, TK, NC, NPW, BF16>;
   constexpr int BM = G::BM, BN = G::BN;
   // old C rows the general epilogue loads together: as registers allow
-  constexpr int EG = G::NW > 8 ? 1 : Loop::kVgprs == 128 ? 4 : (BN > 2 ? 32 / BN : 16);
+  constexpr int EG = G::NW > 8 ? 1 : Loop::kVgprs <= 128 ? 4 : (BN > 2 ? 32 / BN : 16);
   WSG_LDS uint32_t* full = (WSG_LDS uint32_t*)smem;
   WSG_LDS uint32_t* empty = full + kMaxStages;
   WSG_LDS uint32_t* abort_flag = full + 2 * kMaxStages;
@@ -1861,8 +1864,8 @@ template <int UNUSED = 0>
 __global__ void __launch_bounds__(1024) ws_empty_kernel(KernelArgs) {}
 
 // Waves per SIMD a kernel's register allocation must leave room for: what its
-// streaming K loop is laid out for (kVgprs: 256, 168 or 128 registers a wave
-// are two, three or four waves per SIMD; the traced twin of a kernel held to
+// streaming K loop is laid out for (kVgprs: 256, 168, 128 or 80 registers a wave
+// are two, three, four or six waves per SIMD; the traced twin of a kernel held to
 // 128 runs the roll loop, laid out for the same), else one workgroup (what the
 // compiler assumes without the bound).
 template <int TM, int TN, int TK, int NC, int NPW, bool BF16, bool TRACE>

@@ -298,3 +298,17 @@ def test_plan_size_limits(M, N, K, status):
     assert s == status, w.ws_gemm_status_str(s)
     if s == w.WS_OK:
         assert info.tiles == -(-M // 256) * -(-N // 128) and info.iters == -(-K // 64)
+
+
+@pytest.mark.parametrize("tile,np_,nc,resident", [
+    ((32, 32, 32), 1, 1, 8), ((32, 32, 32), 2, 1, 8), ((32, 32, 64), 1, 1, 6), ((32, 32, 64), 2, 1, 5),
+    ((64, 64, 32), 4, 4, 3),
+])
+def test_small_tiles_share_a_cu(tile, np_, nc, resident):
+    """The kernels of the smallest tiles live on the workgroups that share a CU: their
+    registers must leave room for as many, in the general kernel too."""
+    for dtype in ("bf16", "f16"):
+        for M in (16 * resident * tile[0], 16 * resident * tile[0] - 1):
+            s, info = w.ws_gemm_plan(M, 16 * tile[1], 4 * tile[2], cfg(tile, 2, np_, nc, dtype), 256, 0)
+            assert s == w.WS_OK and info.tiles == 256 * resident
+            assert info.grid == info.tiles, (dtype, info.ragged, info.grid // 256)
