@@ -212,22 +212,23 @@ ws_gemm_config part_of(const ws_gemm_config& c, int tm, int tn) {
   return k;
 }
 
-// Workgroups of k's kernel that a CU runs, as its registers allow, when there are `tiles` of them.
-int per_cu(const ws_gemm_config& k, const KernelIndex::Slot& kernel, int64_t tiles, int cus) {
+// Workgroups of k's kernel that a CU runs when there are `tiles` of them.
+int per_cu(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
+  int v = 0, a = 0;
+  kernel_regs(k, general, &v, &a);
   const int waves = k.consumer_waves + k.producer_waves;
-  const int64_t fit = 4 * wsg::waves_per_simd_by_regs(kernel.vgprs, kernel.agprs) / waves;
-  const int64_t want = (tiles + cus - 1) / cus;
+  const int64_t fit = 4 * wsg::waves_per_simd_by_regs(v, a) / waves, want = (tiles + cus - 1) / cus;
   return (int)(want < fit ? want : fit);
 }
 
 // Time (ns per 64 of K) of a launch of `tiles` tiles of k, planned as plan_launch plans it.
-int64_t launch_cost(const ws_gemm_config& k, const KernelIndex::Slot& kernel, int64_t tiles, int cus) {
-  const int64_t one = wsg::tile_cost(k.tile_m, k.tile_n, k.tile_k, k.consumer_waves, k.producer_waves, k.stages);
-  if (tiles <= cus) return one;
-  const int lds = wsg::kPlanHeaderBytes + 2 * k.stages * k.tile_k * (k.tile_m + k.tile_n);
-  const int u = wsg::used_per_cu(
-      tiles, cus, wsg::resident_per_cu(lds, k.consumer_waves + k.producer_waves, kernel.vgprs, kernel.agprs));
+int64_t launch_cost(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
+  int v = 0, a = 0;
+  kernel_regs(k, general, &v, &a);
+  const int64_t lds = wsg::kPlanHeaderBytes + 2ll * k.stages * k.tile_k * (k.tile_m + k.tile_n);
+  const int u = wsg::used_per_cu(tiles, cus, wsg::resident_per_cu(lds, k.consumer_waves + k.producer_waves, v, a));
   const int64_t want = (tiles + cus - 1) / cus, rounds = (tiles + (int64_t)cus * u - 1) / ((int64_t)cus * u);
+  const int64_t one = wsg::tile_cost(k.tile_m, k.tile_n, k.tile_k, k.consumer_waves, k.producer_waves, k.stages);
   return rounds * wsg::shared_cost(one, k.consumer_waves, k.producer_waves, (int)(want < u ? want : u));
 }
 
@@ -243,13 +244,12 @@ void each_part(const ws_gemm_config& c, int cus, int general, int64_t limit, Cou
     for (int tn = c.tile_n; tn >= least; tn /= 2) {
       if (tm == c.tile_m && tn == c.tile_n) continue;
       ws_gemm_config k = part_of(c, tm, tn);
-      const KernelIndex::Slot* kernel = find_slot(k, 0, wsg::kModeGemm, general);
-      if (!kernel) continue;
+      if (!find_kernel(k, 0, wsg::kModeGemm, general)) continue;
       const int64_t tiles = count(k);
       if (c.producer_waves > 0)  // the synchronous kernel's depth says whether it overlaps: kept
         k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n),
-                                    2ll * c.tile_k * (k.tile_m + k.tile_n), per_cu(k, *kernel, tiles, cus));
-      const int64_t cost = launch_cost(k, *kernel, tiles, cus);
+                                    2ll * c.tile_k * (k.tile_m + k.tile_n), per_cu(k, general, tiles, cus));
+      const int64_t cost = launch_cost(k, general, tiles, cus);
       if (cost < limit) {
         f(k, cost);
         limit = cost;
@@ -281,8 +281,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
   const Launch& whole = out->launch[0];
   // costs of the whole problem in ns
   const int64_t slabs = (K + 63) / 64;
-  const KernelIndex::Slot& kernel = *find_slot(c, 0, wsg::kModeGemm, general);
-  const int64_t whole_cost = launch_cost(c, kernel, whole.plan.tiles, cus) * slabs;
+  const int64_t whole_cost = launch_cost(c, general, whole.plan.tiles, cus) * slabs;
   int64_t best = whole_cost * wsg::kPartitionGainNum / wsg::kPartitionGainDen;  // what another partition must not exceed
   ws_gemm_config part{}, rest{};
   each_part(c, cus, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
@@ -297,7 +296,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
       // all whole tiles, or as many rows (columns) of them as whole rounds hold
       const int64_t r = t == 1 ? rounds * cus / cols : rows, q = t == 2 ? rounds * cus / rows : cols;
       if (r < 1 || q < 1 || (r * c.tile_m >= M && q * c.tile_n >= N)) continue;
-      const int64_t block = launch_cost(c, kernel, r * q, cus) * slabs + wsg::kSecondLaunchNs;
+      const int64_t block = launch_cost(c, general, r * q, cus) * slabs + wsg::kSecondLaunchNs;
       if (block >= best) continue;
       each_part(c, cus, general, (best - block) / slabs,
                 [&](const ws_gemm_config& k) {

@@ -134,16 +134,12 @@ inline int resident_per_cu(int64_t lds, int waves, int vgprs, int agprs) {
 // workgroups would need four rounds of five, four need four rounds of four).
 inline int used_per_cu(int64_t tiles, int num_cus, int occ) {
   int use = 1;
-  const uint64_t n = (uint64_t)tiles;
-  uint64_t best = ~0ull, slots = 0;
-  for (int u = 1; u <= occ && slots < n; ++u) {  // one round of u: more of them only share
-    slots += (uint64_t)num_cus;
-    // 32-bit division where it fits: a call that allocates nothing plans every time
-    const uint64_t rounds = slots < n ? (n >> 31 ? (n + slots - 1) / slots
-                                                 : (uint32_t)(n + slots - 1) / (uint32_t)slots)
-                                      : 1;
-    if (rounds * (uint64_t)u <= best) {
-      best = rounds * (uint64_t)u;
+  int64_t best = -1;
+  for (int u = 1; u <= occ; ++u) {
+    const int64_t slots_u = (int64_t)num_cus * u;
+    const int64_t cost = ((tiles + slots_u - 1) / slots_u) * u;
+    if (best < 0 || cost <= best) {
+      best = cost;
       use = u;
     }
   }
