@@ -212,26 +212,6 @@ ws_gemm_config part_of(const ws_gemm_config& c, int tm, int tn) {
   return k;
 }
 
-// Workgroups of k's kernel that a CU runs when there are `tiles` of them.
-int per_cu(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
-  int v = 0, a = 0;
-  kernel_regs(k, general, &v, &a);
-  const int waves = k.consumer_waves + k.producer_waves;
-  const int64_t fit = 4 * wsg::waves_per_simd_by_regs(v, a) / waves, want = (tiles + cus - 1) / cus;
-  return (int)(want < fit ? want : fit);
-}
-
-// Time (ns per 64 of K) of a launch of `tiles` tiles of k, planned as plan_launch plans it.
-int64_t launch_cost(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
-  int v = 0, a = 0;
-  kernel_regs(k, general, &v, &a);
-  const int64_t lds = wsg::kPlanHeaderBytes + 2ll * k.stages * k.tile_k * (k.tile_m + k.tile_n);
-  const int u = wsg::used_per_cu(tiles, cus, wsg::resident_per_cu(lds, k.consumer_waves + k.producer_waves, v, a));
-  const int64_t want = (tiles + cus - 1) / cus, rounds = (tiles + (int64_t)cus * u - 1) / ((int64_t)cus * u);
-  const int64_t one = wsg::tile_cost(k.tile_m, k.tile_n, k.tile_k, k.consumer_waves, k.producer_waves, k.stages);
-  return rounds * wsg::shared_cost(one, k.consumer_waves, k.producer_waves, (int)(want < u ? want : u));
-}
-
 // Calls f(config, cost) for every compiled part of c's tile (the whole tile
 // left out) that is cheaper than `limit`: `count(config)` tiles of it.
 // 32 x 32 parts have one consumer wave and are for tiles of one consumer wave
@@ -243,22 +223,30 @@ void each_part(const ws_gemm_config& c, int cus, int general, int64_t limit, Cou
   for (int tm = c.tile_m; tm >= least; tm /= 2)
     for (int tn = c.tile_n; tn >= least; tn /= 2) {
       if (tm == c.tile_m && tn == c.tile_n) continue;
-      ws_gemm_config k = part_of(c, tm, tn);
-      if (!find_kernel(k, 0, wsg::kModeGemm, general)) continue;
-      const int64_t tiles = count(k);
-      if (c.producer_waves > 0)  // the synchronous kernel's depth says whether it overlaps: kept
-        k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n),
-                                    2ll * c.tile_k * (k.tile_m + k.tile_n), per_cu(k, general, tiles, cus));
-      const int64_t cost = launch_cost(k, general, tiles, cus);
-      if (cost < limit) {
+      const ws_gemm_config k = part_of(c, tm, tn);
+      const int64_t cost = wsg::tiles_cost(count(k), tm, tn, cus);
+      if (cost < limit && find_kernel(k, 0, wsg::kModeGemm, general)) {
         f(k, cost);
         limit = cost;
       }
     }
 }
 
-// Plan of part k on the M x N x K problem.
-bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& k, int cus, int general, Launch* l) {
+// Workgroups of k's kernel that a CU runs when there are `tiles` of them.
+int per_cu(const ws_gemm_config& k, int general, int64_t tiles, int cus) {
+  int v = 0, a = 0;
+  kernel_regs(k, general, &v, &a);
+  const int waves = k.consumer_waves + k.producer_waves;
+  const int64_t fit = 4 * wsg::waves_per_simd_by_regs(v, a) / waves, want = (tiles + cus - 1) / cus;
+  return (int)(want < fit ? want : fit);
+}
+
+// Plan of `tiles` tiles of part k of c on the M x N x K problem.
+bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, ws_gemm_config k, int64_t tiles, int cus,
+               int general, Launch* l) {
+  if (c.producer_waves > 0)  // the synchronous kernel's depth says whether it overlaps: kept
+    k.stages = wsg::part_stages(c.stages, 2ll * c.tile_k * (c.tile_m + c.tile_n),
+                                2ll * c.tile_k * (k.tile_m + k.tile_n), per_cu(k, general, tiles, cus));
   wsg::PlanOut plan;
   if (wsg::plan_launch(plan_in(M, N, K, k, cus, 0, general), &plan) != wsg::kPlanOk) return false;
   *l = Launch{find_kernel(k, 0, wsg::kModeGemm, general)->fn, k, general, plan, -1, -1};
@@ -279,9 +267,9 @@ bool plan_part(int64_t M, int64_t N, int64_t K, const ws_gemm_config& k, int cus
 void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cus, int general, bool plain_block,
                 Run* out) {
   const Launch& whole = out->launch[0];
-  // costs of the whole problem in ns
+  // costs of the whole problem: part_cost units are ns per 64 of K
   const int64_t slabs = (K + 63) / 64;
-  const int64_t whole_cost = launch_cost(c, general, whole.plan.tiles, cus) * slabs;
+  const int64_t whole_cost = wsg::tiles_cost(whole.plan.tiles, c.tile_m, c.tile_n, cus) * slabs;
   int64_t best = whole_cost * wsg::kPartitionGainNum / wsg::kPartitionGainDen;  // what another partition must not exceed
   ws_gemm_config part{}, rest{};
   each_part(c, cus, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
@@ -296,7 +284,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
       // all whole tiles, or as many rows (columns) of them as whole rounds hold
       const int64_t r = t == 1 ? rounds * cus / cols : rows, q = t == 2 ? rounds * cus / rows : cols;
       if (r < 1 || q < 1 || (r * c.tile_m >= M && q * c.tile_n >= N)) continue;
-      const int64_t block = launch_cost(c, general, r * q, cus) * slabs + wsg::kSecondLaunchNs;
+      const int64_t block = wsg::tiles_cost(r * q, c.tile_m, c.tile_n, cus) * slabs + wsg::kSecondLaunchNs;
       if (block >= best) continue;
       each_part(c, cus, general, (best - block) / slabs,
                 [&](const ws_gemm_config& k) {
@@ -325,7 +313,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
     }
     const int cm = rows_best * (c.tile_m / rest.tile_m), cn = cols_best * (c.tile_n / rest.tile_n);
     const int64_t tiles = tiles_of(M, N, rest) - (int64_t)cm * cn;
-    if (!plan_part(M, N, K, rest, cus, general, &e)) return;
+    if (!plan_part(M, N, K, c, rest, tiles, cus, general, &e)) return;
     e.corner_m = cm;
     e.corner_n = cn;
     e.plan.tiles = (int32_t)tiles;
@@ -333,7 +321,7 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
     e.plan.rounds = (int32_t)((tiles + e.plan.grid - 1) / e.plan.grid);
     e.plan.xcd_remap = e.plan.grid % 8 == 0;
   } else if (part.tile_m > 0) {
-    if (!plan_part(M, N, K, part, cus, general, &run.launch[0])) return;
+    if (!plan_part(M, N, K, c, part, tiles_of(M, N, part), cus, general, &run.launch[0])) return;
   } else {
     return;
   }

@@ -115,37 +115,6 @@ inline int waves_per_simd_by_regs(int vgprs, int agprs) {
   return w < kMaxWavesPerSimd ? w : kMaxWavesPerSimd;
 }
 
-// Workgroups that a CU can hold, by LDS, wave slots and registers (the 4 SIMDs
-// of a CU offer 4 x (waves per SIMD) wave slots, which the waves of resident
-// workgroups share).
-inline int resident_per_cu(int64_t lds, int waves, int vgprs, int agprs) {
-  int occ = (int)(kLdsLimit / lds);
-  if (kMaxWavesPerCu / waves < occ) occ = kMaxWavesPerCu / waves;
-  const int by_regs = 4 * waves_per_simd_by_regs(vgprs, agprs) / waves;
-  if (by_regs < occ) occ = by_regs;
-  if (kMaxWgsPerCu < occ) occ = kMaxWgsPerCu;
-  return occ < 1 ? 1 : occ;
-}
-
-// Of the occ workgroups a CU can hold, use the count u that minimises
-// rounds x u (workgroups sharing a CU progress about u times slower), the
-// largest on a tie: a last round that only part of the slots take costs a
-// whole round of the shared CUs (4096 tiles on 256 CUs: five resident
-// workgroups would need four rounds of five, four need four rounds of four).
-inline int used_per_cu(int64_t tiles, int num_cus, int occ) {
-  int use = 1;
-  int64_t best = -1;
-  for (int u = 1; u <= occ; ++u) {
-    const int64_t slots_u = (int64_t)num_cus * u;
-    const int64_t cost = ((tiles + slots_u - 1) / slots_u) * u;
-    if (best < 0 || cost <= best) {
-      best = cost;
-      use = u;
-    }
-  }
-  return use;
-}
-
 // DMA warps per MATH warp of a wave arrangement (consumer waves nc, producer
 // waves np, requested split; 0 requests the one the wave counts imply), or
 // -1 when no kernel has that arrangement.  0 for the synchronous kernel.
@@ -217,8 +186,32 @@ inline int plan_launch(const PlanIn& in, PlanOut* out) {
   if (tm * tn >= (1ll << 31)) return kPlanInvalid;
   const int tiles = (int)(tm * tn);
   const int waves = nc + np;
-  const int occ = in.wgs_per_cu > 0 ? in.wgs_per_cu : resident_per_cu(lds, waves, in.vgprs, in.agprs);
-  const int use = used_per_cu(tiles, in.num_cus, occ);
+  int occ = in.wgs_per_cu;
+  if (occ <= 0) {
+    occ = (int)(kLdsLimit / lds);
+    if (kMaxWavesPerCu / waves < occ) occ = kMaxWavesPerCu / waves;
+    // the 4 SIMDs of a CU offer 4 x (waves per SIMD) wave slots, which the
+    // waves of resident workgroups share
+    const int by_regs = 4 * waves_per_simd_by_regs(in.vgprs, in.agprs) / waves;
+    if (by_regs < occ) occ = by_regs;
+    if (kMaxWgsPerCu < occ) occ = kMaxWgsPerCu;
+  }
+  if (occ < 1) occ = 1;
+  // Of the occ workgroups a CU can hold, use the count u that minimises
+  // rounds x u (workgroups sharing a CU progress about u times slower), the
+  // largest on a tie: a last round that only part of the slots take costs a
+  // whole round of the shared CUs (4096 tiles on 256 CUs: five resident
+  // workgroups would need four rounds of five, four need four rounds of four).
+  int use = 1;
+  int64_t best = -1;
+  for (int u = 1; u <= occ; ++u) {
+    const int64_t slots_u = (int64_t)in.num_cus * u;
+    const int64_t cost = ((tiles + slots_u - 1) / slots_u) * u;
+    if (best < 0 || cost <= best) {
+      best = cost;
+      use = u;
+    }
+  }
   int64_t slots = (int64_t)in.num_cus * use;
   const int grid = (int)(tiles < slots ? tiles : slots);
   const int xcd_remap = (grid % 8 == 0) ? 1 : 0;  // the remap needs whole XCD groups
@@ -261,45 +254,21 @@ inline int plan_launch(const PlanIn& in, PlanOut* out) {
 // so the result is the same to the bit; a part loads more operand bytes per
 // product, which the rule below weighs against the idle CUs.
 //
-// Cost (ns) of 64 of K on one tile of TM x TN by a workgroup that has its CU to
-// itself: what the tile takes when its operands are there, or the latency of a
-// K-iteration where the ring is too short to cover it.  Measured (full launches,
-// bf16, register path, 1:1) / this function:
-//   four consumer waves   T_K = 64, slots 2, 3, 4    T_K = 32, slots 2, 3, 4, 6
-//     64x64    380 300 260     / 373 293 253       567 541 393 298 / 573 543 393 293
-//     128x64   469 366 329     / 433 367 367       616 637 478 399 / 633 603 453 367
-//     128x128  585 481 462     / 558 558 558       762 577 516 548 / 729 699 558 558
-//     256x128  934 830         / 941 941          1032 1040 895 897 / 941 941 941 941
-//   eight consumer waves, 256x256  1508 / 1610    1806 1577 1548  / 1610 1610 1610
-//   one consumer wave     T_K = 64, slots 2, 3, 4    T_K = 32, slots 2, 3, 4
-//     32x32    317 248 250     / 358 278 238       489 470 400 / 558 528 378
-//     64x64    458 365 358     / 435 370 370       596 577 508 / 635 605 455
-//   synchronous (load, then multiply), four waves: T_K = 64 64x64 717, 128x128 1048,
-//   256x256 2063 / 720 991 2071; T_K = 32 1234 1435 2567 / 1255 1522 2590; one wave:
-//   T_K = 64 32x32 621, 64x64 870 / 676 814; T_K = 32 1143 1384 / 1212 1350
-// two producer groups within 10 % of these.
-inline int64_t tile_cost(int tm, int tn, int tk, int consumer_waves, int producer_waves, int stages) {
-  const int64_t area = (int64_t)tm * tn;
-  if (producer_waves == 0) return (tk < 64 ? 1166 : 630) + area * (consumer_waves == 1 ? 450 : 220) / 10000;
-  int64_t work = 80 + area * 175 / 10000 + 3 * (tm + tn) / 4;
-  if (consumer_waves == 1) work = work * 3 / 2;
-  const int64_t wait = tk < 64 ? (stages < 3 ? 450 : stages < 4 ? 420 : stages < 6 ? 270 : 170)
-                               : (stages < 3 ? 250 : stages < 4 ? 170 : 130);
-  return work > wait + work / 2 ? work : wait + work / 2;
+// Cost of 64 of K on one tile of TM x TN (ns per CU; workgroups that share a
+// CU take turns), from full launches of 4 + 4 waves at T_K = 64, measured /
+// this line: 64x64 260 / 248, 128x64 400 / 367, 128x128 520 / 559,
+// 256x128 900 / 941, 256x256 (8 + 4 waves) 1670 / 1611.
+inline int64_t part_cost(int tm, int tn) {
+  return 80 + (int64_t)tm * tn * 175 / 10000 + 3 * (tm + tn) / 4;
 }
 
-// Time of `n` workgroups that share a CU, in units of one alone: the
-// synchronous kernel's leave it idle most of the time (three cost what one
-// does, 128x128x64 1048 1057 1424 for one, two, three), those of one consumer
-// wave a part of it (64x64x64 458 572 726 902), four consumer waves less
-// (64x64x64 380 567, 128x128x32 762 1233).
-inline int64_t shared_cost(int64_t cost, int consumer_waves, int producer_waves, int n) {
-  if (producer_waves == 0) return n <= 3 ? cost : cost * n / 3;
-  return consumer_waves == 1 ? cost * (3 + n) / 4 : cost * (1 + 2 * n) / 3;
+// Time of `tiles` tiles, in part_cost units per 64 of K.
+inline int64_t tiles_cost(int64_t tiles, int tm, int tn, int num_cus) {
+  return (tiles + num_cus - 1) / num_cus * part_cost(tm, tn);
 }
 
-// Another partition must beat whole tiles by a tenth (tile_cost is good to 15 %
-// either way).  Measured, whole tiles -> parts: 1024^3 with 128x128x64 tiles (64 tiles,
+// Another partition must beat whole tiles by a tenth (the line above is good to
+// 7 %).  Measured, whole tiles -> parts: 1024^3 with 128x128x64 tiles (64 tiles,
 // three slots) 11.8 us -> 7.2 us as 64x64 parts, the same with K = 8192 62 -> 32
 // us; 2048x2048x4096 with 256x256x64 tiles (64 tiles) 80 -> 39 us as 128x128
 // parts; 256^3 with 64x64x32 tiles of one consumer wave 7.2 -> 4.9 us as 32x32

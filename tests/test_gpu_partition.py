@@ -41,7 +41,7 @@ RESTS = [
     ((4100, 4104, 264), T256, "bf16", "registers"),
     ((4100, 4104, 1288), T256, "f16", "registers"),
     ((4100, 2056, 1280), ((256, 128, 64), 3, 4, 4), "bf16", "registers"),
-    ((1068, 2024, 1280), ((64, 64, 32), 3, 2, 1), "bf16", "registers"),
+    ((1100, 1032, 5120), ((64, 64, 64), 3, 1, 1), "bf16", "registers"),
 ]
 CASES = [c + (1,) for c in PARTS] + [c + (2,) for c in RESTS]
 GUARD, SENTINEL = 4096, -7.0
