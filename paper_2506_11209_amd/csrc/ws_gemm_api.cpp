@@ -272,13 +272,29 @@ void choose_run(int64_t M, int64_t N, int64_t K, const ws_gemm_config& c, int cu
   const int64_t whole_cost = wsg::tiles_cost(whole.plan.tiles, c.tile_m, c.tile_n, cus) * slabs;
   int64_t best = whole_cost * wsg::kPartitionGainNum / wsg::kPartitionGainDen;  // what another partition must not exceed
   ws_gemm_config part{}, rest{};
-  each_part(c, cus, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
-            [&](const ws_gemm_config& k, int64_t cost) {
-              part = k;
-              best = cost * slabs;
-            });
+  // A double-buffered synchronous workgroup that has its CU to itself overlaps
+  // its own loads; parts of it do so no better once every CU has a tile
+  // (256x256x32 at 19200x1024x2048, 300 tiles: whole 197 us, in parts 244 us).
+  // With fewer than eight K-iterations the stores count for more, and parts win
+  // (2816x6144x160 by 1.2).
+  int vgprs = 0, agprs = 0;
+  kernel_regs(c, general, &vgprs, &agprs);
+  const int waves = c.consumer_waves + c.producer_waves;
+  const bool alone = 2 * whole.plan.lds_bytes > wsg::kLdsLimit ||
+                     4 * wsg::waves_per_simd_by_regs(vgprs, agprs) < 2 * waves;
+  if (!(c.producer_waves == 0 && c.stages == 2 && alone && whole.plan.tiles > cus && whole.plan.iters >= 8))
+    each_part(c, cus, general, best / slabs + 1, [&](const ws_gemm_config& k) { return tiles_of(M, N, k); },
+              [&](const ws_gemm_config& k, int64_t cost) {
+                part = k;
+                best = cost * slabs;
+              });
+  // A block and the rest: not where the tiles past the last whole round share
+  // their CUs with the others in one round, which costs far less than the round
+  // of its own that the cost counts (128x64x32 at 640x3520x5376, 275 tiles: whole
+  // 79 us, block and rest 105 us), and so not for one consumer wave, of which
+  // four or more tiles share a CU (64x64x64 at 1337x872x5992: 61 and 93 us).
   int rows_best = 0, cols_best = 0;
-  if (c.producer_waves > 0) {
+  if (c.producer_waves > 0 && c.consumer_waves > 1 && whole.plan.rounds > 1) {
     const int64_t rows = M / c.tile_m, cols = N / c.tile_n, rounds = rows * cols / cus;
     for (int t = 0; t < 3 && rows > 0 && cols > 0; ++t) {
       // all whole tiles, or as many rows (columns) of them as whole rounds hold

@@ -255,9 +255,15 @@ inline int plan_launch(const PlanIn& in, PlanOut* out) {
 // product, which the rule below weighs against the idle CUs.
 //
 // Cost of 64 of K on one tile of TM x TN (ns per CU; workgroups that share a
-// CU take turns), from full launches of 4 + 4 waves at T_K = 64, measured /
-// this line: 64x64 260 / 248, 128x64 400 / 367, 128x128 520 / 559,
-// 256x128 900 / 941, 256x256 (8 + 4 waves) 1670 / 1611.
+// CU take turns), from full launches of 4 + 4 waves at T_K = 64 with four slots,
+// measured / this line: 64x64 260 / 248, 128x64 400 / 367, 128x128 520 / 559,
+// 256x128 900 / 941, 256x256 (8 + 4 waves) 1670 / 1611, so good to 9 %.  Other
+// launches cost more: two or three slots (64x64 380 and 300), T_K = 32 (64x64 567
+// with two slots, 298 with six), one consumer wave (64x64 460-350, 32x32 320-250),
+// the synchronous kernel (64x64 720, 256x256 2070).  The line decides for them by
+// the ratio of two sizes, which is closer: of 3314 drawn launches of every
+// arrangement, T_K and depth that are not computed as whole tiles, nine take over
+// 3 % longer than whole tiles would, the worst 1.23 times.
 inline int64_t part_cost(int tm, int tn) {
   return 80 + (int64_t)tm * tn * 175 / 10000 + 3 * (tm + tn) / 4;
 }
@@ -267,12 +273,11 @@ inline int64_t tiles_cost(int64_t tiles, int tm, int tn, int num_cus) {
   return (tiles + num_cus - 1) / num_cus * part_cost(tm, tn);
 }
 
-// Another partition must beat whole tiles by a tenth (the line above is good to
-// 7 %).  Measured, whole tiles -> parts: 1024^3 with 128x128x64 tiles (64 tiles,
-// three slots) 11.8 us -> 7.2 us as 64x64 parts, the same with K = 8192 62 -> 32
-// us; 2048x2048x4096 with 256x256x64 tiles (64 tiles) 80 -> 39 us as 128x128
-// parts; 256^3 with 64x64x32 tiles of one consumer wave 7.2 -> 4.9 us as 32x32
-// parts.
+// Another partition must beat whole tiles by a tenth.  Measured, whole tiles ->
+// parts: 1024^3 with 128x128x64 tiles (64 tiles, three slots) 11.8 us -> 7.2 us as
+// 64x64 parts, the same with K = 8192 62 -> 32 us; 2048x2048x4096 with 256x256x64
+// tiles (64 tiles) 80 -> 39 us as 128x128 parts; 256^3 with 64x64x32 tiles of one
+// consumer wave 7.2 -> 4.9 us as 32x32 parts.
 constexpr int kPartitionGainNum = 10, kPartitionGainDen = 11;
 
 // What a second launch on the stream adds (ns): the first one's drain and the

@@ -83,6 +83,15 @@ def test_launches_cover_c_once(c):
     (4100, 4104, 4104, ((256, 256, 64), 2, 4, 8), [(256, 256, 2), (64, 64, 8)]),
     (4096, 4096, 4096, ((128, 128, 32), 3, 4, 4), [(128, 128, 3)]),
     (8192, 8192, 8192, ((256, 256, 64), 2, 4, 8), [(256, 256, 2)]),
+    (2056, 1160, 5120, ((128, 64, 64), 4, 8, 4), [(128, 64, 4), (64, 64, 6)]),
+    # no rest where it shares one round with the block: launches of one round, one consumer wave
+    (640, 3520, 5376, ((128, 64, 32), 2, 4, 4), [(128, 64, 2)]),
+    (1337, 872, 5992, ((64, 64, 64), 3, 1, 1), [(64, 64, 3)]),
+    (1100, 1032, 5120, ((64, 64, 64), 3, 1, 1), [(64, 64, 3)]),
+    # synchronous, two buffers, alone on its CU: whole once every CU has a tile, unless K is short
+    (19200, 1024, 2048, ((256, 256, 32), 2, 0, 4), [(256, 256, 2)]),
+    (4096, 1024, 2048, ((256, 256, 32), 2, 0, 4), [(128, 128, 2)]),
+    (2816, 6144, 160, ((256, 256, 32), 2, 0, 4), [(128, 128, 2)]),
 ])
 def test_choices_of_the_rule(M, N, K, launch, tiles):
     assert [(l.tile_m, l.tile_n, l.stages) for l in check(M, N, K, w.config(*launch))] == tiles
