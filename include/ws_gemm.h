@@ -33,9 +33,9 @@
  * same to the bit (every element takes its products in the same order), and
  * the plan a handle reports stays that of its whole tiles.  A block of whole
  * tiles may also run first and the rest, in parts, as a second launch of the
- * same run.  Calibration kernels and traced runs always take whole tiles, as the
- * plan counts them.  ws_gemm_query_launches reports what a run launches, ws_gemm_set_partition keeps a handle to the
- * requested tile and ring.
+ * same run.  Calibration kernels and traced runs always take whole tiles, as
+ * the plan counts them.  ws_gemm_query_launches reports what a run launches,
+ * ws_gemm_set_partition keeps a handle to the requested tile and ring.
  *
  * Data layout: A, B and C are dense and row-major (leading dimensions K, N
  * and N).  A and B hold IEEE binary16 (WS_F16) or bfloat16 (WS_BF16)
